@@ -64,7 +64,7 @@ def _ensure_built():
 
 
 def kernel_of(info):
-    return "pair_kernel" if info["steps"] == 2 else "step_kernel"
+    return {1: "step_kernel", 2: "pair_kernel"}.get(info["steps"], "march_kernel")
 
 
 def _summary(name):
@@ -470,9 +470,9 @@ def main():
         # direct launches, or the last 1 000 launches of a 2 000-step run
         "roofline": roofline_block("fp32", info, nodes, t["event_ms_per_step"],
                                    f"traffic_{kernel_of(info).split('_')[0]}_fp32_2048x512.txt",
-                                   "pair_kernel_fp32_2048x512_20steps_kernel_trace.txt"
+                                   f"{kernel_of(info)}_fp32_2048x512_20steps_kernel_trace.txt"
                                    if t["launch"] == "direct groups"
-                                   else "pair_kernel_fp32_2048x512_kernel_trace.txt",
+                                   else f"{kernel_of(info)}_fp32_2048x512_kernel_trace.txt",
                                    tag="2048x512"),
     }
     if not args.no_extra:

@@ -315,7 +315,9 @@ int lbm_batch_set_streams(lbm_batch *b, int32_t n);
 void lbm_batch_destroy(lbm_batch *b);
 
 /* Compiled tile shapes of the step kernel: count, and one shape: a workgroup
- * of bx x by threads, each updating nx consecutive axial nodes in ny rows. */
+ * of bx x by threads, each updating nx consecutive axial nodes in ny rows
+ * (shapes of more than two steps per launch choose their rows by the grid:
+ * ny = 1). */
 int lbm_tile_shape_count(void);
 int lbm_tile_shape(int32_t index, int32_t *bx, int32_t *by, int32_t *ny, int32_t *nx);
 /* All properties of a shape: info[0..n-1] of (bx, by, ny, nx, waves per SIMD
@@ -326,7 +328,10 @@ int lbm_tile_shape(int32_t index, int32_t *bx, int32_t *by, int32_t *ny, int32_t
  * Shapes with 2 steps per launch run two time steps of eq. (1) per kernel
  * launch on an LDS-resident 64 x (by * ny) tile with a one-node frame,
  * bit-identical to two one-step launches, on every edge rule (with periodic
- * x edges the frame wraps to the other end of the domain). */
+ * x edges the frame wraps to the other end of the domain).  Shapes with more
+ * (S) run up to S steps per launch with waves that march up strips of
+ * 64 - 2 (S - 1) columns, the intermediate states in registers (LDS holds
+ * the property table), as bit-identical and on as many edge rules. */
 int lbm_tile_shape_info(int32_t index, int32_t *info, int32_t n);
 /* Select the launch variant of a handle (synchronises; EINVAL for an unknown
  * index, or any shape but 0 on a single-buffer handle, whose in-place kernel

@@ -1,10 +1,10 @@
 // lbm_api.hip -- single-jet C-ABI (include/lbm.h) on one HIP device.
 //
 // A handle owns (or borrows) two population buffers and a stream, plus a few
-// small device arrays: the descriptor, a one-entry tile list, the property
-// table, the inlet rows and an instability flag.  Steps are enqueued as one
+// small device arrays: the descriptor, the property table, the inlet rows and an instability flag.  Steps are enqueued as one
 // launch of the step kernel each, or as HIP graphs of k launches followed
 // by the descriptor advance.
+#include <algorithm>
 #include <mutex>
 
 #include "lbm_runtime.hpp"
@@ -37,8 +37,6 @@ struct lbm_handle {
   bool own_stream = false;
   // device arrays
   JetDesc *d_desc = nullptr;
-  int32_t *d_tiles = nullptr;
-  BatchHdr *d_hdr = nullptr;
   int32_t *d_flag = nullptr;
   float4 *d_table = nullptr;
   float4 *d_inlet = nullptr;
@@ -77,16 +75,16 @@ int upload_desc(lbm_handle *h) {
 
 int set_shape(lbm_handle *h, int shape) {
   int n;
-  tile_shapes(&n);
+  const TileShape *shapes = tile_shapes(&n);
   if (shape < 0 || shape >= n) return LBM_EINVAL;
   if (h->layout == LBM_LAYOUT_SINGLE && shape != 0) return LBM_EINVAL;
   int32_t tx;
-  h->ntiles = tiles_of(&h->cfg, shape, &tx);
+  h->desc.tile_rows = marches(shapes[shape]) ? march_rows({{h->cfg.nx, h->cfg.nr}}, shape) : 0;
+  h->ntiles = tiles_of(h->cfg.nx, h->cfg.nr, shape, h->desc.tile_rows, &tx);
   h->grid = (h->ntiles + 7) / 8 * 8;
   h->shape = shape;
   h->desc.tiles_x = tx;
-  int32_t tl[2] = {0, h->ntiles};
-  LBM_HIP(hipMemcpyAsync(h->d_tiles, tl, sizeof tl, hipMemcpyHostToDevice, h->stream));
+  h->desc.ntiles = h->ntiles;
   return upload_desc(h);
 }
 
@@ -120,8 +118,6 @@ void release(lbm_handle *h) {
   drop_graph(h);
   h->scratch.release();
   if (h->d_desc) (void)hipFree(h->d_desc);
-  if (h->d_tiles) (void)hipFree(h->d_tiles);
-  if (h->d_hdr) (void)hipFree(h->d_hdr);
   if (h->d_flag) (void)hipFree(h->d_flag);
   if (h->d_table) (void)hipFree(h->d_table);
   if (h->d_inlet) (void)hipFree(h->d_inlet);
@@ -143,7 +139,8 @@ int upload_inlet(lbm_handle *h, const std::vector<float4> &rows, int32_t n_t) {
   h->d_inlet = p;
   h->desc.inlet = p;
   h->desc.n_t = n_t;
-  int rc = upload_desc(h);
+  int rc = launch_inlet(h->stream, p, rows.size());
+  if (!rc) rc = upload_desc(h);
   if (rc) return rc;
   // the inlet ghosts of the current buffer follow the new rows
   if ((rc = launch_ghost_fill(h->prec, h->stream, h->d_desc, &h->cfg, h->step, view_of(h, h->step)))) return rc;
@@ -195,19 +192,15 @@ int create_common(const lbm_config *cfg, void *dev_buf, size_t bytes, void *stre
   }
   std::vector<float4> table = make_table(&h->cfg);
   bool ok = hipMalloc(&h->d_desc, sizeof(JetDesc)) == hipSuccess &&
-            hipMalloc(&h->d_tiles, 2 * sizeof(int32_t)) == hipSuccess &&
-            hipMalloc(&h->d_hdr, sizeof(BatchHdr)) == hipSuccess &&
             hipMalloc(&h->d_flag, sizeof(int32_t)) == hipSuccess &&
             hipMalloc(&h->d_table, table.size() * sizeof(float4)) == hipSuccess;
   if (!ok) {
     release(h);
     return LBM_ENOMEM;
   }
-  BatchHdr hdr{1, {0, 0, 0}};
   const int32_t zero = 0;
   ok = hipMemcpy(h->d_table, table.data(), table.size() * sizeof(float4),
                  hipMemcpyHostToDevice) == hipSuccess &&
-       hipMemcpy(h->d_hdr, &hdr, sizeof hdr, hipMemcpyHostToDevice) == hipSuccess &&
        hipMemcpy(h->d_flag, &zero, sizeof zero, hipMemcpyHostToDevice) == hipSuccess;
   if (!ok) {
     release(h);
@@ -223,7 +216,7 @@ int create_common(const lbm_config *cfg, void *dev_buf, size_t bytes, void *stre
   std::vector<float4> rows;
   make_inlet(&h->cfg, 0, nullptr, nullptr, nullptr, rows);
   if ((rc = upload_inlet(h, rows, 1)) ||
-      (rc = set_shape(h, h->layout == LBM_LAYOUT_SINGLE ? 0 : default_tile_shape(h->prec)))) {
+      (rc = set_shape(h, h->layout == LBM_LAYOUT_SINGLE ? 0 : default_tile_shape(h->prec, (int64_t)cfg->nx * cfg->nr)))) {
     release(h);
     return rc;
   }
@@ -249,38 +242,42 @@ int create_common(const lbm_config *cfg, void *dev_buf, size_t bytes, void *stre
 // handle's shape.
 int one_step(lbm_handle *h, int32_t koff, int32_t tog) {
   if (h->layout == LBM_LAYOUT_SINGLE)
-    return launch_aa_step(h->prec, h->grid, h->stream, h->d_desc, h->d_tiles, h->d_hdr, koff,
+    return launch_aa_step(h->prec, h->grid, h->stream, h->d_desc, nullptr, nullptr, koff,
                           h->d_flag);
-  return launch_step(h->shape, h->prec, h->grid, h->stream, h->d_desc, h->d_tiles, h->d_hdr,
-                     koff, tog, 1, h->d_flag);
+  return launch_step(h->shape, h->prec, big_table(&h->cfg), h->grid, h->stream, h->d_desc,
+                     nullptr, nullptr, koff, tog, 1, h->d_flag);
 }
 
-// The launches of a group of k steps on `st`: with a two-step shape, k / 2
-// pair launches (and one single step if k is odd), starting koff0 steps past
-// the descriptor's step0 with its flip toggled by tog0; then, if `advance`,
-// the descriptor advance (koff0 = tog0 = 0 then).
-int enqueue_group(lbm_handle *h, int32_t k, bool pair, hipStream_t st, int32_t koff0 = 0,
-                  int32_t tog0 = 0, bool advance = true) {
+// Steps one launch of the handle's shape advances.
+int32_t steps_per_launch(const lbm_handle *h) {
+  int nsh;
+  return h->layout == LBM_LAYOUT_SINGLE ? 1 : tile_shapes(&nsh)[h->shape].steps;
+}
+
+// The launches of a group of k steps on `st`: with a shape of several steps
+// per launch, launches of that many and one of the rest, starting koff0
+// steps past the descriptor's step0 with its flip toggled by tog0; then, if
+// `advance`, the descriptor advance (koff0 = tog0 = 0 then).
+int enqueue_group(lbm_handle *h, int32_t k, hipStream_t st, int32_t koff0 = 0, int32_t tog0 = 0,
+                  bool advance = true) {
   int rc = LBM_OK;
-  const int32_t np = pair ? k / 2 : 0;
-  for (int32_t q = 0; q < np && !rc; ++q)
-    rc = launch_step(h->shape, h->prec, h->grid, st, h->d_desc, h->d_tiles, h->d_hdr,
-                     koff0 + 2 * q, tog0 ^ (q & 1), 2, h->d_flag);
-  for (int32_t q = 2 * np; q < k && !rc; ++q)
+  const int32_t spl = steps_per_launch(h);
+  for (int32_t q = 0; q < k && !rc; q += spl)
     rc = h->layout == LBM_LAYOUT_SINGLE
-             ? launch_aa_step(h->prec, h->grid, st, h->d_desc, h->d_tiles, h->d_hdr, koff0 + q,
+             ? launch_aa_step(h->prec, h->grid, st, h->d_desc, nullptr, nullptr, koff0 + q,
                               h->d_flag)
-             : launch_step(h->shape, h->prec, h->grid, st, h->d_desc, h->d_tiles, h->d_hdr,
-                           koff0 + q, tog0 ^ (np & 1), 1, h->d_flag);
-  if (!rc && advance) rc = launch_advance(st, h->d_desc, h->d_hdr, 1, k, np);
+             : launch_step(h->shape, h->prec, big_table(&h->cfg), h->grid, st, h->d_desc,
+                           nullptr, nullptr, koff0 + q, tog0 ^ flip_toggles(q, spl),
+                           std::min(spl, k - q), h->d_flag);
+  if (!rc && advance) rc = launch_advance(st, h->d_desc, nullptr, 1, k, spl);
   return rc;
 }
 
 // Capture k steps as one graph (enqueue_group's launches).
-int capture_group(lbm_handle *h, int32_t k, bool pair) {
+int capture_group(lbm_handle *h, int32_t k) {
   hipGraph_t g;
   LBM_HIP(hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
-  const int crc = enqueue_group(h, k, pair, h->stream);
+  const int crc = enqueue_group(h, k, h->stream);
   const hipError_t e = hipStreamEndCapture(h->stream, &g);
   if (crc || e != hipSuccess) return crc ? crc : LBM_EDEVICE;
   const hipError_t ei = hipGraphInstantiate(&h->gexec, g, nullptr, nullptr, 0);
@@ -300,8 +297,7 @@ int prepare_graph(lbm_handle *h) {
   if (h->graph_k <= 0) return LBM_OK;
   if (h->gexec && h->gexec_k == h->graph_k && h->gexec_shape == h->shape) return LBM_OK;
   drop_graph(h);
-  int nsh;
-  const int rc = capture_group(h, h->graph_k, tile_shapes(&nsh)[h->shape].steps == 2);
+  const int rc = capture_group(h, h->graph_k);
   if (rc) return rc;
   // (an optimisation only: the graph also uploads itself at its first launch)
   (void)hipGraphUpload(h->gexec, h->stream);
@@ -321,7 +317,7 @@ int prepare_graph(lbm_handle *h) {
 // Brings the device descriptor's step0 and flip to the host's.
 int catch_up(lbm_handle *h) {
   if (h->base == h->step && h->dflip == h->flip) return LBM_OK;
-  const int rc = launch_advance(h->stream, h->d_desc, h->d_hdr, 1, (int32_t)(h->step - h->base),
+  const int rc = launch_advance(h->stream, h->d_desc, nullptr, 1, (int32_t)(h->step - h->base), 0,
                                 h->flip ^ h->dflip);
   if (rc) return rc;
   h->base = h->step;
@@ -330,8 +326,7 @@ int catch_up(lbm_handle *h) {
 }
 
 int launch_steps(lbm_handle *h, int64_t n) {
-  int nsh;
-  const bool pair = tile_shapes(&nsh)[h->shape].steps == 2;
+  const int32_t spl = steps_per_launch(h);
   int rc;
   while (n > 0) {
     const bool graph = h->graph_k > 0 && n >= h->graph_k;
@@ -340,27 +335,25 @@ int launch_steps(lbm_handle *h, int64_t n) {
     if (graph) {
       if (!h->gexec || h->gexec_k != h->graph_k || h->gexec_shape != h->shape) {
         drop_graph(h);
-        if ((rc = capture_group(h, h->graph_k, pair))) return rc;
+        if ((rc = capture_group(h, h->graph_k))) return rc;
       }
       LBM_HIP(hipGraphLaunch(h->gexec, h->stream));
       h->step += h->graph_k;
       h->base += h->graph_k;
-      if (pair) {
-        h->flip ^= (h->graph_k / 2) & 1;
-        h->dflip ^= (h->graph_k / 2) & 1;
-      }
+      h->flip ^= flip_toggles(h->graph_k, spl);
+      h->dflip ^= flip_toggles(h->graph_k, spl);
       n -= h->graph_k;
-    } else if (pair) {
+    } else if (spl > 1) {
       // the rest (fewer steps than a graph holds) as directly launched
       // steps: a graph's launches, offset from the descriptor, and no
       // advance (the device starts on the first kernel while the host
       // enqueues the rest)
-      const int32_t m = (int32_t)std::min<int64_t>(n, 1 << 20);
-      if ((rc = enqueue_group(h, m, true, h->stream, (int32_t)(h->step - h->base),
+      const int32_t m = (int32_t)std::min<int64_t>(n, (1 << 20) / spl * spl);
+      if ((rc = enqueue_group(h, m, h->stream, (int32_t)(h->step - h->base),
                               h->flip ^ h->dflip, false)))
         return rc;
       h->step += m;
-      h->flip ^= (m / 2) & 1;
+      h->flip ^= flip_toggles(m, spl);
       n -= m;
     } else {
       rc = one_step(h, (int32_t)(h->step - h->base), h->flip ^ h->dflip);

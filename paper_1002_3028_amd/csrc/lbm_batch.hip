@@ -161,10 +161,11 @@ struct lbm_batch {
   struct Cohort {
     int prec = LBM_PREC_FP32, shape = 0;
     int32_t grid = 0;
+    bool big_table = false;  // a jet's property table exceeds the marching kernel's LDS copy
   };
   std::vector<Cohort> cohorts[2];
-  // (k, shape, grid, cohort, copy, storage form)
-  std::map<std::tuple<int, int, int, int, int, int>, hipGraphExec_t> graphs;
+  // (k, shape, grid, cohort, copy, storage form, big table)
+  std::map<std::tuple<int, int, int, int, int, int, bool>, hipGraphExec_t> graphs;
   // cohorts alternate between the batch's stream and a second one, so that
   // one cohort's launches fill the device while the other's start or drain
   static constexpr int MAX_STREAMS = 4;
@@ -176,10 +177,16 @@ struct lbm_batch {
 
 namespace {
 
-// The requested (or default) shape for a storage form.
-int pick_shape(const lbm_batch *b, int prec) {
+// The requested (or default) shape for a cohort of `nodes` nodes.
+int pick_shape(const lbm_batch *b, int prec, int64_t nodes) {
   if (b->layout == LBM_LAYOUT_SINGLE) return 0;  // the in-place kernel's tiles
-  return b->shape >= 0 ? b->shape : default_tile_shape(prec);
+  return b->shape >= 0 ? b->shape : default_tile_shape(prec, nodes);
+}
+
+// Steps one launch of a tile shape advances.
+int32_t steps_per_launch(const lbm_batch *b, int shape) {
+  int nsh;
+  return b->layout == LBM_LAYOUT_SINGLE ? 1 : tile_shapes(&nsh)[shape].steps;
 }
 
 bool storage_form(int prec) {
@@ -251,21 +258,32 @@ int rebuild(lbm_batch *b) {
       bytes.push_back(0);
       meta.emplace_back();
     }
-    if (jets.back().empty()) {
-      meta.back().prec = sl.prec;
-      meta.back().shape = pick_shape(b, sl.prec);
-    }
-    const int shape = meta.back().shape;
-    sl.shape = shape;
-    int32_t tx;
-    const int nt = tiles_of(&sl.cfg, shape, &tx);
-    sl.desc.tiles_x = tx;
+    if (jets.back().empty()) meta.back().prec = sl.prec;
+    meta.back().big_table |= big_table(&sl.cfg);
     sl.desc.step0 = sl.step;
     sl.desc.flip = sl.flip;
     jets.back().push_back(sl.desc);
-    start.back().push_back(start.back().back() + nt);
     bytes.back() += sl.bytes;
     b->active.push_back(s);
+  }
+  // the cohorts' tile lists
+  int nsh;
+  const TileShape *shapes = tile_shapes(&nsh);
+  for (size_t c = 0; c < jets.size(); ++c) {
+    int64_t nodes = 0;
+    for (const JetDesc &d : jets[c]) nodes += (int64_t)d.nx * d.nr;
+    const int shape = meta[c].shape = pick_shape(b, meta[c].prec, nodes);
+    int32_t rows = 0;
+    if (marches(shapes[shape])) {
+      MarchJets sizes;
+      for (const JetDesc &d : jets[c]) sizes.emplace_back(d.nx, d.nr);
+      rows = march_rows(sizes, shape);
+    }
+    for (JetDesc &d : jets[c]) {
+      b->slots[d.slot].shape = shape;
+      d.tile_rows = rows;
+      start[c].push_back(start[c].back() + tiles_of(d.nx, d.nr, shape, rows, &d.tiles_x));
+    }
   }
   // the groups that read this copy last, and the uploads from its staging
   // queued before them, must be done before either is rewritten
@@ -278,7 +296,7 @@ int rebuild(lbm_batch *b) {
   size_t jo = 0, to = 0;  // staging offsets
   for (int32_t c = 0; c < nh; ++c) {
     const int32_t n = c < b->n_cohorts ? (int32_t)jets[c].size() : 0;
-    L.hh[c] = BatchHdr{n, {0, 0, 0}};
+    L.hh[c] = BatchHdr{n, n > 0 ? start[c][n] : 0, {0, 0}};
     if (n > 0) std::memcpy(L.hj + jo, jets[c].data(), n * sizeof(JetDesc));
     if (n > 0) std::memcpy(L.ht + to, start[c].data(), (n + 1) * sizeof(int32_t));
     else L.ht[to] = 0;
@@ -313,10 +331,10 @@ int run_group(lbm_batch *b, int32_t k, int32_t c, hipStream_t st) {
   const lbm_batch::Cohort &m = b->cohorts[b->copy][c];
   const int shape = m.shape, prec = m.prec;
   const int32_t grid = m.grid;
-  int nsh;
-  const int32_t np = tile_shapes(&nsh)[shape].steps == 2 ? k / 2 : 0;
+  const int32_t spl = steps_per_launch(b, shape);
   const int32_t ms = (int32_t)b->slots.size();
-  auto key = std::make_tuple((int)k, shape, (int)grid, (int)c, (int)b->copy, prec);
+  auto key = std::make_tuple((int)k, shape, (int)grid, (int)c, (int)b->copy, prec,
+                             m.big_table);
   auto it = b->graphs.find(key);
   if (it == b->graphs.end()) {
     const Lists L = lists_of(b, b->copy);
@@ -327,15 +345,13 @@ int run_group(lbm_batch *b, int32_t k, int32_t c, hipStream_t st) {
     hipGraph_t g;
     LBM_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
     int rc = LBM_OK;
-    // k / 2 pair launches with a two-step shape (one single step if k is
-    // odd), else k single steps
-    for (int32_t q = 0; q < np && !rc; ++q)
-      rc = launch_step(shape, prec, grid, cs, jets, tiles, hdr, 2 * q, q & 1, 2, b->d_flags);
-    for (int32_t q = 2 * np; q < k && !rc; ++q)
+    // launches of spl steps and one of the rest
+    for (int32_t q = 0; q < k && !rc; q += spl)
       rc = b->layout == LBM_LAYOUT_SINGLE
                ? launch_aa_step(prec, grid, cs, jets, tiles, hdr, q, b->d_flags)
-               : launch_step(shape, prec, grid, cs, jets, tiles, hdr, q, np & 1, 1, b->d_flags);
-    if (!rc) rc = launch_advance(cs, jets, hdr, ms, k, np);
+               : launch_step(shape, prec, m.big_table, grid, cs, jets, tiles, hdr, q,
+                             flip_toggles(q, spl), std::min(spl, k - q), b->d_flags);
+    if (!rc) rc = launch_advance(cs, jets, hdr, ms, k, spl);
     const hipError_t e = hipStreamEndCapture(cs, &g);
     if (rc || e != hipSuccess) return rc ? rc : LBM_EDEVICE;
     hipGraphExec_t ex;
@@ -434,7 +450,7 @@ int lbm_batch_create(size_t budget_bytes, int32_t max_slots, int32_t precision,
   if (ok) {
     *b->h_zero = 0;
     std::vector<int32_t> zeros(max_slots, 0);
-    std::vector<BatchHdr> hz(2 * mc, BatchHdr{0, {0, 0, 0}});
+    std::vector<BatchHdr> hz(2 * mc, BatchHdr{0, 0, {0, 0}});
     std::vector<int32_t> tz(2 * mc * (max_slots + 1), 0);
     ok = hipMemcpy(b->d_flags, zeros.data(), max_slots * sizeof(int32_t),
                    hipMemcpyHostToDevice) == hipSuccess &&
@@ -546,9 +562,6 @@ int lbm_batch_admit(lbm_batch *b, const lbm_config *cfg, int32_t n_t, const doub
   d.target = target_steps;
   d.step0 = 0;
   d.slot = s;
-  int32_t tx;
-  tiles_of(&sl.cfg, pick_shape(b, prec), &tx);
-  d.tiles_x = tx;
   // Uploads and initialisation are queued on the batch's stream, behind the
   // groups in flight.  Those no longer touch this slot's memory: the jet it
   // held last was retired only once its last group had finished, and later
@@ -563,6 +576,7 @@ int lbm_batch_admit(lbm_batch *b, const lbm_config *cfg, int32_t n_t, const doub
                          hipMemcpyHostToDevice, b->stream));
   LBM_HIP(hipMemcpyAsync(b->d_flags + s, b->h_zero, sizeof(int32_t), hipMemcpyHostToDevice,
                          b->stream));
+  if ((rc = launch_inlet(b->stream, sl.d_inlet, rows.size()))) return rc;
   const float4 u0 =
       make_float4((float)cfg->rho0, (float)cfg->ux0, (float)cfg->ur0, (float)cfg->T0);
   for (int64_t q = n_buffers(b->layout) - 1; q >= 0 && !rc; --q) {
@@ -602,17 +616,14 @@ int lbm_batch_run(lbm_batch *b, int32_t k_steps) {
   LBM_HIP(hipEventRecord(b->done[b->seq % lbm_batch::RING], b->stream));
   LBM_HIP(hipEventRecord(b->copy_done[b->copy], b->stream));
   b->copy_used[b->copy] = true;
-  // mirror of the advance kernel: every pair a jet took in full toggled its flip
-  int nsh;
-  const TileShape *shapes = tile_shapes(&nsh);
+  // mirror of the advance kernel
   bool finished = false;
   for (int32_t s : b->active) {
     Slot &sl = b->slots[s];
-    const int64_t np = shapes[sl.shape].steps == 2 ? k_steps / 2 : 0;
     if (sl.step >= sl.target) continue;
-    if (np > 0 && sl.target - sl.step >= 2)
-      sl.flip ^= (int32_t)(std::min<int64_t>(np, (sl.target - sl.step) / 2) & 1);
-    sl.step = std::min<int64_t>(sl.step + k_steps, sl.target);
+    const int64_t n = std::min<int64_t>(k_steps, sl.target - sl.step);
+    sl.flip ^= flip_toggles(n, steps_per_launch(b, sl.shape));
+    sl.step += n;
     if (sl.step >= sl.target) {
       sl.done_seq = b->seq;
       finished = true;

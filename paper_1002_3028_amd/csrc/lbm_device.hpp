@@ -83,7 +83,7 @@ __device__ __forceinline__ gptr<const T> as_global(const T *p) {
 struct alignas(16) JetDesc {
   void *buf[2];            // population buffers; state after s steps in buf[(s + flip) & 1]
   const float4 *table;     // (M_nu, dM_nu, M_alpha, dM_alpha) at each grid point
-  const float4 *inlet;     // n_t rows of nr (ux, ur, T, 0)
+  const float4 *inlet;     // n_t rows of nr (f_1, f_5, f_8, g_0) entering column 0
   int64_t plane;           // elements per population plane (pitch * nr)
   int64_t step0;           // step count of the launch with koff = 0
   int64_t target;          // the jet stops at this step count
@@ -93,16 +93,59 @@ struct alignas(16) JetDesc {
   float r0, nu0, alpha0, c18;      // c18 = 18 (C_s Delta)^2
   float inv_prt, G, t_lo, t_scale; // t_scale = (table_n - 1) / (t_hi - t_lo)
   float rho_ref, g4_ref;
-  int32_t flip;                    // toggled by every launch that advances two steps
+  int32_t flip;                    // toggled by every launch that advances an even number of steps
+  int32_t tile_rows;               // rows of one wave's tile (march_kernel)
+  int32_t ntiles;                  // tiles of the jet
   float wallT[4];                  // NaN: adiabatic
   float eq[4][4];                  // EQ side: rho, ux, ur, T
 };
 
-// Batch header in device memory: number of jets in the tile list.  The tile
-// list itself is tile_start[0..njets] (prefix sums of the jets' tile counts).
+// Parity of the launches of an even number of steps (each of which toggles a
+// jet's flip) when n steps are taken in launches of spl steps and one of the
+// rest.
+__host__ __device__ inline int32_t flip_toggles(int64_t n, int32_t spl) {
+  const int64_t rest = n % spl;
+  return (int32_t)(((n / spl) * (spl - 1) + (rest > 0 ? rest - 1 : 0)) & 1);
+}
+
+// Batch header in device memory: number of jets in the tile list and its
+// length.  The list itself is tile_start[0..njets] (prefix sums of the jets'
+// tile counts).
 struct BatchHdr {
-  int32_t njets;
-  int32_t pad[3];
+  int32_t njets, ntiles;
+  int32_t pad[2];
+};
+
+// The jets of a launch.  A launch for one jet has no header and no tile list
+// (null): everything it needs is in the one descriptor, and a launch starts
+// two dependent loads earlier.
+struct TileList {
+  const JetDesc *jets;
+  const int32_t *tile_start;
+  int32_t njets, ntiles;
+  __device__ __forceinline__ TileList(const JetDesc *j, const int32_t *ts, const BatchHdr *hdr)
+      : jets(j), tile_start(ts) {
+    if (hdr) {
+      njets = hdr->njets;
+      ntiles = hdr->ntiles;
+    } else {
+      njets = 1;
+      ntiles = j[0].ntiles;
+    }
+  }
+  // The jet of tile t, and t made the tile's number within it.
+  __device__ __forceinline__ int32_t find(int32_t &t) const {
+    int32_t lo = 0;
+    if (njets > 1) {  // last jet whose first tile is <= t
+      int32_t hi = njets - 1;
+      while (lo < hi) {
+        const int32_t mid = (lo + hi + 1) >> 1;
+        if (tile_start[mid] <= t) lo = mid; else hi = mid - 1;
+      }
+      t -= tile_start[lo];
+    }
+    return lo;
+  }
 };
 
 // Partial sums of the FP64 conservation reduction.
@@ -249,9 +292,45 @@ struct NoHook {
   __device__ void operator()() const {}
 };
 
-template <class H = NoHook>
-__device__ __forceinline__ bool collide(const JetDesc &d, float rinv, float r2,
-                                        float (&f)[9], float (&g)[4], const H &hook = H()) {
+// The property table's entry i in global memory: (M_nu, dM_nu, M_alpha, dM_alpha).
+struct GlobalTable {
+  static constexpr bool in_lds = false;
+  const float4 *p;
+  __device__ __forceinline__ float4 operator()(int i) const {
+    const gptr<const float> q = as_global((const float *)p) + 4 * i;
+    return make_float4(q[0], q[1], q[2], q[3]);
+  }
+};
+
+// D: the descriptor, or a copy of its physics (Physics).
+struct Physics {
+  float t_lo, t_scale, nu0, alpha0, c18, inv_prt, G;
+  int32_t table_n, hoop;
+  __device__ explicit Physics(const JetDesc &d)
+      : t_lo(d.t_lo), t_scale(d.t_scale), nu0(d.nu0), alpha0(d.alpha0), c18(d.c18),
+        inv_prt(d.inv_prt), G(d.G), table_n(d.table_n), hoop(d.hoop) {}
+};
+
+template <class D, class H, class Tab>
+__device__ __forceinline__ bool collide(const D &d, float rinv, float r2,
+                                        float (&f)[9], float (&g)[4], const H &hook,
+                                        const Tab &table) {
+  // eq. (6): multiplier tables, linear on a uniform grid, clamped; the gather
+  // goes out first, the work below that does not need it hides its latency
+  const float T = (g[0] + g[1]) + (g[2] + g[3]);
+  float w;
+  float4 te;
+  const auto gather = [&] {
+    const float x = __builtin_amdgcn_fmed3f((T - d.t_lo) * d.t_scale, 0.0f,
+                                            (float)(d.table_n - 1));  // NaN -> 0
+    const int i0 = min((int)x, d.table_n - 2);
+    w = x - (float)i0;
+    te = table(i0);
+  };
+  if constexpr (Tab::in_lds) {
+    gather();
+    __builtin_amdgcn_sched_barrier(0);
+  }
   // eq. (2)
   // (partial sums shared between rho, m and Q)
   const float s13 = f[1] + f[3], s24 = f[2] + f[4];
@@ -260,18 +339,9 @@ __device__ __forceinline__ bool collide(const JetDesc &d, float rinv, float r2,
   const float rho = ((f[0] + s13) + s24) + sd;
   const float mx = (f[1] - f[3]) + (s58 - s67);
   const float mr = (f[2] - f[4]) + ((f[5] + f[6]) - (f[7] + f[8]));
-  const float T = (g[0] + g[1]) + (g[2] + g[3]);
   const float irho = fast_rcp(rho);
   const float ux = mx * irho, ur = mr * irho;
-
-  // eq. (6): multiplier tables, linear on a uniform grid, clamped; the gather
-  // goes out first, the work below that does not need it hides its latency
-  float x = fmaxf((T - d.t_lo) * d.t_scale, 0.0f);  // NaN -> 0
-  x = fminf(x, (float)(d.table_n - 1));
-  const int i0 = max(min((int)x, d.table_n - 2), 0);
-  const float w = x - (float)i0;
-  const gptr<const float> tp = as_global((const float *)d.table) + 4 * i0;
-  const float4 te = make_float4(tp[0], tp[1], tp[2], tp[3]);
+  if constexpr (!Tab::in_lds) gather();
   if constexpr (!__is_same(H, NoHook)) {
     __builtin_amdgcn_sched_barrier(0);
     hook();
@@ -290,6 +360,9 @@ __device__ __forceinline__ bool collide(const JetDesc &d, float rinv, float r2,
   const float jr = (g[1] - g[3]) - T * ur;
   const float qn = fast_sqrt(2.0f * (qxx * qxx + 2.0f * qxr * qxr + qrr * qrr));
 
+  // (an LDS gather takes about as long as the work since it was issued; the
+  // compiler by itself waits for it at once)
+  if constexpr (Tab::in_lds) __builtin_amdgcn_sched_barrier(0);
   const float nu = d.nu0 * (te.x + w * te.y);
   const float alpha = d.alpha0 * (te.z + w * te.w);
   const float tau_nu = 0.5f + 3.0f * nu;
@@ -342,7 +415,14 @@ __device__ __forceinline__ bool collide(const JetDesc &d, float rinv, float r2,
   g[1] = __builtin_fmaf(g[1], omg, Eg + hr);  // +r
   g[3] = __builtin_fmaf(g[3], omg, Eg - hr);  // -r
 
-  return (rho > 0.0f) && (rho < __builtin_inff()) && (fabsf(T) < __builtin_inff());
+  // rho positive and finite, T finite
+  return __builtin_amdgcn_classf(rho, 0x180) & __builtin_amdgcn_classf(T, 0x1f8);
+}
+
+template <class H = NoHook>
+__device__ __forceinline__ bool collide(const JetDesc &d, float rinv, float r2,
+                                        float (&f)[9], float (&g)[4], const H &hook = H()) {
+  return collide(d, rinv, r2, f, g, hook, GlobalTable{d.table});
 }
 
 // ---------------------------------------------------------------------------
@@ -369,6 +449,15 @@ struct Dst {
   }
 };
 
+// Entry j of an inlet row, the populations (f_1, f_5, f_8, g_0) that enter
+// there, read through a global pointer, or held by the caller (who asks for
+// its own row only).
+__device__ __forceinline__ float4 inlet_at(const float4 *in, int j) {
+  const gptr<const float> q = as_global((const float *)in) + 4 * j;
+  return make_float4(q[0], q[1], q[2], q[3]);
+}
+__device__ __forceinline__ float4 inlet_at(const float4 &held, int) { return held; }
+
 // x-side rule for plane p taken from column ip of row jr; (i_land, j_land)
 // is the receiving node (for a mirrored pull, the node of the edge row).
 template <class C, class S>
@@ -381,10 +470,9 @@ __device__ __forceinline__ float pull_x(const JetDesc &d, const S &s, int p, int
       return s.load(d, p, ip < 0 ? ip + d.nx : ip - d.nx, jr);
     case BC_OUTFLOW:
       return s.load(d, p, d.nx - 1, jr);
-    case BC_INLET: {
-      const gptr<const float> qp = as_global((const float *)inrow) + 4 * jr;
-      const float4 q = make_float4(qp[0], qp[1], qp[2], qp[3]);
-      return eq_plane(p, 1.0f, q.x, q.y, q.z);
+    case BC_INLET: {  // (the links that enter: 1, 5, 8 and g_0)
+      const float4 q = inlet_at(inrow, jr);
+      return p == 1 ? q.x : p == 5 ? q.y : p == 8 ? q.z : q.w;
     }
     case BC_WALL: {
       const int po = p < 9 ? opp9(p) : 9 + opp4(p - 9);
@@ -535,23 +623,19 @@ __device__ __forceinline__ float wall_g(const JetDesc &d, int side, float v) {
   return tw == tw ? -v + 0.5f * tw : v;
 }
 
-// Inlet row entry j as (ux, ur, T, 0), read through a global pointer.
-__device__ __forceinline__ float4 inlet_at(const float4 *in, int j) {
-  const gptr<const float> q = as_global((const float *)in) + 4 * j;
-  return make_float4(q[0], q[1], q[2], 0.0f);
-}
 
 // After the collision of node (i, j), write the ghost values of the next
 // step that this node is the source of, following the edge rules (r side
 // first; a mirrored pull goes through the x rule at the edge row).  Ghosts
 // of equilibrium sides are constant and written once by the ghost fill.
-// `in` is the inlet row of the next step.
+// `in` is the inlet row of the next step (or its entry at row j: only that
+// one is asked for).
 // O is any destination with put(d, p, i, j, v): the next buffer, or the
 // LDS image of the intermediate state of a two-step launch.
-template <class C, class O>
+template <class C, class O, class In>
 __device__ __forceinline__ void ghost_epilogue(const JetDesc &d, const O &o, int i, int j,
                                                const float (&f)[9], const float (&g)[4],
-                                               const float4 *in, uint32_t key) {
+                                               const In &in, uint32_t key) {
   // a copy of population k takes k's key; a computed value its own plane's
   const auto K = [&](int k) { return plane_key(key, k); };
   const int nx = d.nx, nr = d.nr;
@@ -587,10 +671,10 @@ __device__ __forceinline__ void ghost_epilogue(const JetDesc &d, const O &o, int
   if (i == 0) {  // ghost column -1 (rows 0..nr-1): links 1, 5, 8 and g0 (+x)
     if (x0 == BC_INLET) {
       const float4 q = inlet_at(in, j);
-      o.put(d, 1, -1, j, feq_link(1, 1.0f, q.x, q.y), K(1));
-      o.put(d, 5, -1, j, feq_link(5, 1.0f, q.x, q.y), K(5));
-      o.put(d, 8, -1, j, feq_link(8, 1.0f, q.x, q.y), K(8));
-      o.put(d, 9, -1, j, geq_link(0, q.z, q.x, q.y), K(9));
+      o.put(d, 1, -1, j, q.x, K(1));
+      o.put(d, 5, -1, j, q.y, K(5));
+      o.put(d, 8, -1, j, q.z, K(8));
+      o.put(d, 9, -1, j, q.w, K(9));
     } else if (x0 == BC_WALL) {
       o.put(d, 1, -1, j, f[3], K(3));
       if (j >= 1) o.put(d, 5, -1, j - 1, f[7], K(7));
@@ -630,7 +714,7 @@ __device__ __forceinline__ void ghost_epilogue(const JetDesc &d, const O &o, int
     if (i == nx - 1 && x0 == BC_PERIODIC) o.put(d, 5, -1, -1, f[8], K(8));
     if (i == 0 && x0 == BC_INLET) {
       const float4 q = inlet_at(in, 0);
-      o.put(d, 5, -1, -1, feq_link(8, 1.0f, q.x, q.y), K(5));
+      o.put(d, 5, -1, -1, q.z, K(5));
     }
     if (i == 0 && x0 == BC_WALL) o.put(d, 5, -1, -1, f[6], K(6));
     // (nx, -1) link 6 <- x rule of link 7 at column nx, row 0
@@ -643,7 +727,7 @@ __device__ __forceinline__ void ghost_epilogue(const JetDesc &d, const O &o, int
     if (i == nx - 1 && x0 == BC_PERIODIC) o.put(d, 8, -1, nr, f[5], K(5));
     if (i == 0 && x0 == BC_INLET) {
       const float4 q = inlet_at(in, nr - 1);
-      o.put(d, 8, -1, nr, feq_link(5, 1.0f, q.x, q.y), K(8));
+      o.put(d, 8, -1, nr, q.y, K(8));
     }
     if (i == 0 && x0 == BC_WALL) o.put(d, 8, -1, nr, f[7], K(7));
     // (nx, nr) link 7 <- x rule of link 6 at column nx, row nr-1

@@ -5,6 +5,65 @@
 
 namespace lbmx {
 
+// ---- kernels of no storage form ----------------------------------------------
+// Moves every jet's step0 by delta (clamped at the target); ends a captured
+// group of steps so that the same graph serves the next group.  The group's
+// launches took spl steps each and the last one the rest: flip_toggles of
+// them swapped the roles of a jet's buffers.  spl = 0: one jet, whose flip
+// is toggled by `flip`.
+__global__ void advance_kernel(JetDesc *__restrict__ jets, const BatchHdr *__restrict__ hdr,
+                               int32_t delta, int32_t spl, int32_t flip) {
+  const int32_t q = blockIdx.x * blockDim.x + threadIdx.x;
+  if (q < (hdr ? hdr->njets : 1)) {
+    const int64_t s0 = jets[q].step0, tg = jets[q].target;
+    const int64_t s = s0 + delta < tg ? s0 + delta : tg;
+    jets[q].flip ^= spl > 0 ? flip_toggles(s - s0, spl) : flip;
+    jets[q].step0 = s;
+  }
+}
+
+// Inlet entries (ux, ur, T, 0) made the populations that enter the domain
+// there: the equilibria of links 1, 5, 8 and +x at density 1.
+__global__ void inlet_kernel(float4 *__restrict__ rows, int64_t n) {
+  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (q >= n) return;
+  const float4 v = rows[q];
+  rows[q] = make_float4(feq_link(1, 1.0f, v.x, v.y), feq_link(5, 1.0f, v.x, v.y),
+                        feq_link(8, 1.0f, v.x, v.y), geq_link(0, v.z, v.x, v.y));
+}
+
+// Reduces the conservation kernel's partial sums the same way.
+__global__ __launch_bounds__(RED_THREADS) void reduce_partials_kernel(
+    const RedPartial *__restrict__ partial, int32_t n, RedPartial *__restrict__ out) {
+  double m = 0.0, e = 0.0, bad = 0.0;
+  for (int q = threadIdx.x; q < n; q += RED_THREADS) {
+    m += partial[q].mass;
+    e += partial[q].energy;
+    bad += partial[q].bad;
+  }
+  __shared__ double sm[RED_THREADS], se[RED_THREADS], sb[RED_THREADS];
+  sm[threadIdx.x] = m;
+  se[threadIdx.x] = e;
+  sb[threadIdx.x] = bad;
+  __syncthreads();
+  for (int w = RED_THREADS / 2; w > 0; w >>= 1) {
+    if ((int)threadIdx.x < w) {
+      sm[threadIdx.x] += sm[threadIdx.x + w];
+      se[threadIdx.x] += se[threadIdx.x + w];
+      sb[threadIdx.x] += sb[threadIdx.x + w];
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) out[0] = RedPartial{sm[0], se[0], sb[0], 0.0};
+}
+
+// Plain streaming copy, 16 B per lane per iteration.
+__global__ __launch_bounds__(256) void copy_kernel(const float4 *__restrict__ src,
+                                                   float4 *__restrict__ dst, int64_t n) {
+  for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < n; q += (int64_t)gridDim.x * 256)
+    dst[q] = src[q];
+}
+
 // ---- validation (same rules the paper's setting implies: tau > 1/2 so that
 // nu, alpha > 0; Pr_t > 0; a symmetry axis only at r = 0) ------------------
 static bool side_ok(int side, int bc) {
@@ -104,6 +163,7 @@ void fill_desc(JetDesc &d, const lbm_config *c) {
   d.rho_ref = (float)c->rho_ref;
   d.g4_ref = (float)(0.25 * c->g_ref);
   d.flip = 0;
+  d.tile_rows = 0;
 }
 
 int make_inlet(const lbm_config *c, int32_t n_t, const double *ux, const double *ur,
@@ -129,7 +189,7 @@ int make_inlet(const lbm_config *c, int32_t n_t, const double *ux, const double 
    {(const void *)&step_kernel<CodecF32, BX, BY, NY, NX, W, CP>,                 \
     (const void *)&step_kernel<CodecF16, BX, BY, NY, NX, W, CP>,                 \
     (const void *)&step_kernel<CodecBF16, BX, BY, NY, NX, W, CP>,                \
-    (const void *)&step_kernel<CodecF16SR, BX, BY, NY, NX, W, CP>}}
+    (const void *)&step_kernel<CodecF16SR, BX, BY, NY, NX, W, CP>}, {}}
 // two steps per launch: 64 x TY tiles, block 64 x NW (lds: the LDS image of
 // FP32 storage; the 16-bit forms keep theirs in the storage type, half that)
 #define LBM_PAIR(TY, NW, W, CP)                                                  \
@@ -137,9 +197,10 @@ int make_inlet(const lbm_config *c, int32_t n_t, const double *ux, const double 
    {(const void *)&pair_kernel<CodecF32, TY, NW, W, CP>,                         \
     (const void *)&pair_kernel<CodecF16, TY, NW, W, CP>,                         \
     (const void *)&pair_kernel<CodecBF16, TY, NW, W, CP>,                        \
-    (const void *)&pair_kernel<CodecF16SR, TY, NW, W, CP>}}
+    (const void *)&pair_kernel<CodecF16SR, TY, NW, W, CP>}, {}}
 
-static const TileShape kShapes[] = {
+static const std::vector<TileShape> &shapes() {
+  static const std::vector<TileShape> table = {
     LBM_SHAPE(64, 4, 1, 1, 1, 0),  LBM_SHAPE(128, 2, 1, 1, 1, 0), LBM_SHAPE(256, 1, 1, 1, 1, 0),
     LBM_SHAPE(64, 8, 1, 1, 1, 0),  LBM_SHAPE(64, 4, 2, 1, 1, 0),  LBM_SHAPE(64, 4, 1, 2, 1, 0),
     LBM_SHAPE(128, 2, 1, 2, 1, 0), LBM_SHAPE(64, 4, 1, 1, 1, 1),  LBM_SHAPE(64, 4, 1, 1, 1, 2),
@@ -154,42 +215,92 @@ static const TileShape kShapes[] = {
     // workgroups per CU, and the 1 024 tiles of a 2048 x 512 jet then fit
     // the resident workgroups at once (no second, partly idle round)
     LBM_PAIR(16, 4, 5, 8),         LBM_PAIR(16, 4, 5, 12),
-};
+    // up to four steps per launch, waves marching up strips
+    kMarch4,
+  };
+  return table;
+}
 #undef LBM_SHAPE
 #undef LBM_PAIR
 
 const TileShape *tile_shapes(int *count) {
-  *count = (int)(sizeof(kShapes) / sizeof(kShapes[0]));
-  return kShapes;
+  *count = (int)shapes().size();
+  return shapes().data();
 }
-// FP32 storage: the two-step kernel on 64 x 8 tiles with f_0 kept in
-// registers (12-plane image, 5 workgroups per CU): the HBM traffic per step
-// halves and the arithmetic still fits under it.  16-bit storage, whose step
-// is arithmetic-limited already: one step per launch.
-int default_tile_shape(int prec) {
+// FP32 storage: from 200 000 nodes in a launch four steps per launch (the
+// marching kernel): measured per step against the two-step kernel, 5.5
+// against 6.0 us on 1024 x 256, 7.5 / 8.9 on 1500 x 375, 9.9 / 13.1 on
+// 2048 x 512 and 32 / 57 on 4096 x 1024, but 5.0 / 4.6 on 1001 x 77 and 4.9
+// / 4.6 on 512 x 128, where a wave's halo rows outnumber its own.  Below, the
+// two-step kernel on 64 x 8 tiles with f_0 kept in registers (12-plane image,
+// 5 workgroups per CU).  16-bit storage: one step per launch.
+int default_tile_shape(int prec, int64_t nodes) {
   if (prec != LBM_PREC_FP32) return 0;
   int n;
   const TileShape *s = tile_shapes(&n);
   for (int q = 0; q < n; ++q)
-    if (s[q].steps == 2 && s[q].by == 4 && s[q].by * s[q].ny == 8 && s[q].cache == 8) return q;
+    if (nodes >= 200000 ? marches(s[q])
+                        : s[q].steps == 2 && s[q].by == 4 && s[q].by * s[q].ny == 8 &&
+                              s[q].cache == 8)
+      return q;
   return 0;
 }
 
-int tiles_of(const lbm_config *c, int shape, int32_t *tiles_x) {
-  const TileShape &s = kShapes[shape];
-  const int tx = (c->nx + s.bx * s.nx - 1) / (s.bx * s.nx);
-  const int ty = (c->nr + s.by * s.ny - 1) / (s.by * s.ny);
+int tiles_of(int32_t nx, int32_t nr, int shape, int32_t rows, int32_t *tiles_x) {
+  const TileShape &s = shapes()[shape];
+  const int w = marches(s) ? s.bx - 2 * (s.steps - 1) : s.bx * s.nx;
+  const int h = s.by * (marches(s) ? rows : s.ny);
+  const int tx = (nx + w - 1) / w;
+  const int ty = (nr + h - 1) / h;
   if (tiles_x) *tiles_x = tx;
   return tx * ty;
 }
 
-int launch_step(int shape, int prec, int grid, hipStream_t st, const JetDesc *jets,
-                const int32_t *tiles, const BatchHdr *hdr, int32_t koff, int32_t tog,
-                int32_t nsteps, int32_t *flags) {
-  const TileShape &s = kShapes[shape];
+// Rows of a wave's tile, for jets marched in one launch.  A wave of R rows
+// does K R + K (K - 1) collisions per column (its own and the halo rows that
+// its neighbours compute too), so tall tiles waste less, but the launch lasts
+// as long as the busiest CU: two workgroups of four waves share a CU (one
+// wave per SIMD leaves a third of the issue slots empty: 0.44 us per
+// collision of a wave alone, 0.33 us with two on the SIMD), and a third has
+// to wait.  The height with the least work on the busiest CU wins: on
+// 2048 x 512 ten rows (468 workgroups, 9.9 us per step), not nine (540
+// workgroups, 12.4) or nineteen (252 workgroups, 11.4).
+int32_t march_rows(const MarchJets &jets, int shape) {
+  const TileShape &s = shapes()[shape];
+  const int w = s.bx - 2 * (s.steps - 1), k = s.steps;
+  const int cus = device_cus();
+  int32_t nr_max = 0;
+  for (const auto &j : jets) nr_max = std::max(nr_max, j.second);
+  int32_t best = 1;
+  double best_t = 0.0;
+  for (int32_t r = 1; r <= (nr_max + s.by - 1) / s.by; ++r) {
+    const int32_t h = s.by * r;
+    int64_t wg = 0;
+    for (const auto &j : jets) wg += (int64_t)((j.first + w - 1) / w) * ((j.second + h - 1) / h);
+    const int64_t per_cu = (wg + cus - 1) / cus;
+    const double t = (double)(k * r + k * (k - 1)) * (0.67 * (per_cu / 2) + 0.44 * (per_cu % 2));
+    if (r == 1 || t < best_t) best = r, best_t = t;
+  }
+  return best;
+}
+
+int device_cus() {
+  int cus = 0, dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      cus <= 0)
+    return 256;
+  return cus;
+}
+
+int launch_step(int shape, int prec, bool big_table, int grid, hipStream_t st,
+                const JetDesc *jets, const int32_t *tiles, const BatchHdr *hdr, int32_t koff,
+                int32_t tog, int32_t nsteps, int32_t *flags) {
+  const TileShape &s = shapes()[shape];
+  const void *fn = (big_table && marches(s) ? s.big : s.fn)[codec_index(prec)];
   void *args[] = {(void *)&jets, (void *)&tiles, (void *)&hdr,   (void *)&koff,
                   (void *)&tog,  (void *)&nsteps, (void *)&flags};
-  LBM_HIP(hipLaunchKernel(s.fn[codec_index(prec)], dim3(grid), dim3(s.bx, s.by), args, 0, st));
+  LBM_HIP(hipLaunchKernel(fn, dim3(grid), dim3(s.bx, s.by), args, 0, st));
   return LBM_OK;
 }
 
@@ -202,7 +313,7 @@ static const void *aa_fn(int prec) {
 }
 
 int resident_workgroups(int shape, int prec, bool single_buffer) {
-  const TileShape &s = kShapes[shape];
+  const TileShape &s = shapes()[shape];
   const void *fn = single_buffer ? aa_fn(prec) : s.fn[codec_index(prec)];
   const int threads = single_buffer ? 256 : s.bx * s.by;
   int per_cu = 0, cus = 0, dev = 0;
@@ -224,9 +335,16 @@ int launch_aa_step(int prec, int grid, hipStream_t st, const JetDesc *jets, cons
 }
 
 int launch_advance(hipStream_t st, JetDesc *jets, const BatchHdr *hdr, int32_t njets_max,
-                   int32_t delta, int32_t npair) {
+                   int32_t delta, int32_t spl, int32_t flip) {
   const int blocks = (njets_max + 63) / 64;
-  hipLaunchKernelGGL(advance_kernel, dim3(blocks), dim3(64), 0, st, jets, hdr, delta, npair);
+  hipLaunchKernelGGL(advance_kernel, dim3(blocks), dim3(64), 0, st, jets, hdr, delta, spl, flip);
+  LBM_HIP(hipGetLastError());
+  return LBM_OK;
+}
+
+int launch_inlet(hipStream_t st, float4 *rows, size_t n) {
+  hipLaunchKernelGGL(inlet_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, rows,
+                     (int64_t)n);
   LBM_HIP(hipGetLastError());
   return LBM_OK;
 }

@@ -93,23 +93,14 @@ __global__ __launch_bounds__(BX *BY) __attribute__((amdgpu_waves_per_eu(W, 8))) 
   constexpr int ES = (int)sizeof(T);
   constexpr int VB = ES * NX;  // bytes per lane per plane
   using VT = typename Pack<T, NX>::vec;
-  const int32_t njets = hdr->njets;
-  const int32_t ntiles = tile_start[njets];
-  const TileWalk tw = tile_walk(ntiles);
+  const TileList list(jets, tile_start, hdr);
+  const TileWalk tw = tile_walk(list.ntiles);
   for (int32_t t = tw.first; t < tw.end; t += tw.stride) {
-    int32_t jid = 0;
-    if (njets > 1) {  // last jet whose first tile is <= t
-      int32_t lo = 0, hi = njets - 1;
-      while (lo < hi) {
-        const int32_t mid = (lo + hi + 1) >> 1;
-        if (tile_start[mid] <= t) lo = mid; else hi = mid - 1;
-      }
-      jid = lo;
-    }
+    int32_t lt = t;
+    const int32_t jid = list.find(lt);
     const JetDesc &d = jets[jid];
     const int64_t step = d.step0 + koff;
     if (step >= d.target) continue;
-    const int32_t lt = t - tile_start[jid];
     const int32_t ty = lt / d.tiles_x;
     const int32_t tx = lt - ty * d.tiles_x;
     const int i0 = (tx * BX + (int)threadIdx.x) * NX;
@@ -326,24 +317,15 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(W, 8)))
   static_assert(TY % NW == 0 && 2 * EH <= 64, "tile rows");
   __shared__ T img[(NPOP - P0) * EH * PAIR_W];
   const int lane = (int)threadIdx.x, wave = (int)threadIdx.y;
-  const int32_t njets = hdr->njets;
-  const int32_t ntiles = tile_start[njets];
-  const TileWalk tw = tile_walk(ntiles);
+  const TileList list(jets, tile_start, hdr);
+  const TileWalk tw = tile_walk(list.ntiles);
   for (int32_t t = tw.first; t < tw.end; t += tw.stride) {
-    int32_t jid = 0;
-    if (njets > 1) {  // last jet whose first tile is <= t
-      int32_t lo = 0, hi = njets - 1;
-      while (lo < hi) {
-        const int32_t mid = (lo + hi + 1) >> 1;
-        if (tile_start[mid] <= t) lo = mid; else hi = mid - 1;
-      }
-      jid = lo;
-    }
+    int32_t lt = t;
+    const int32_t jid = list.find(lt);
     const JetDesc &d = jets[jid];
     const int64_t step = d.step0 + koff;
     if (step >= d.target) continue;
     const bool two = (nsteps > 1) & (step + 1 < d.target);
-    const int32_t lt = t - tile_start[jid];
     const int32_t ty = lt / d.tiles_x;
     const int32_t tx = lt - ty * d.tiles_x;
     const int ia = tx * 64, ja = ty * TY;
@@ -526,23 +508,14 @@ __global__ __launch_bounds__(256) void aa_kernel(
   using T = typename C::T;
   constexpr int ES = (int)sizeof(T);
   const int lane = (int)threadIdx.x, wave = (int)threadIdx.y;
-  const int32_t njets = hdr->njets;
-  const int32_t ntiles = tile_start[njets];
-  const TileWalk tw = tile_walk(ntiles);
+  const TileList list(jets, tile_start, hdr);
+  const TileWalk tw = tile_walk(list.ntiles);
   for (int32_t t = tw.first; t < tw.end; t += tw.stride) {
-    int32_t jid = 0;
-    if (njets > 1) {  // last jet whose first tile is <= t
-      int32_t lo = 0, hi = njets - 1;
-      while (lo < hi) {
-        const int32_t mid = (lo + hi + 1) >> 1;
-        if (tile_start[mid] <= t) lo = mid; else hi = mid - 1;
-      }
-      jid = lo;
-    }
+    int32_t lt = t;
+    const int32_t jid = list.find(lt);
     const JetDesc &d = jets[jid];
     const int64_t step = d.step0 + koff;
     if (step >= d.target) continue;
-    const int32_t lt = t - tile_start[jid];
     const int32_t ty = lt / d.tiles_x;
     const int32_t tx = lt - ty * d.tiles_x;
     const int i = tx * 64 + lane, j = ty * 4 + wave;
@@ -620,24 +593,6 @@ __global__ void ghost_fill_kernel(const JetDesc *__restrict__ dp, int64_t step, 
     if (pi >= 0 && pi < nx && pj >= 0 && pj < nr)
       st.put(d, p, gi, gj, pull_edge<C>(d, st, p, pi, pj, inrow),
              plane_key(sr_key(gi, gj, 0), p));
-  }
-}
-
-// Moves every jet's step0 by delta (clamped at the target); ends a captured
-// group of steps so that the same graph serves the next group.  The group
-// began with npair two-step launches: each that a jet took in full (both
-// steps before its target) swapped the roles of its buffers.
-__global__ void advance_kernel(JetDesc *__restrict__ jets, const BatchHdr *__restrict__ hdr,
-                               int32_t delta, int32_t npair) {
-  const int32_t q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q < hdr->njets) {
-    const int64_t s0 = jets[q].step0, tg = jets[q].target;
-    if (npair > 0 && tg - s0 >= 2) {
-      const int64_t full = (tg - s0) / 2 < npair ? (tg - s0) / 2 : npair;
-      jets[q].flip ^= (int32_t)(full & 1);
-    }
-    const int64_t s = s0 + delta;
-    jets[q].step0 = s < tg ? s : tg;
   }
 }
 
@@ -733,30 +688,6 @@ __global__ __launch_bounds__(RED_THREADS) void conservation_kernel(
   if (threadIdx.x == 0) partial[blockIdx.x] = RedPartial{sm[0], se[0], sb[0], 0.0};
 }
 
-__global__ __launch_bounds__(RED_THREADS) void reduce_partials_kernel(
-    const RedPartial *__restrict__ partial, int32_t n, RedPartial *__restrict__ out) {
-  double m = 0.0, e = 0.0, bad = 0.0;
-  for (int q = threadIdx.x; q < n; q += RED_THREADS) {
-    m += partial[q].mass;
-    e += partial[q].energy;
-    bad += partial[q].bad;
-  }
-  __shared__ double sm[RED_THREADS], se[RED_THREADS], sb[RED_THREADS];
-  sm[threadIdx.x] = m;
-  se[threadIdx.x] = e;
-  sb[threadIdx.x] = bad;
-  __syncthreads();
-  for (int w = RED_THREADS / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) {
-      sm[threadIdx.x] += sm[threadIdx.x + w];
-      se[threadIdx.x] += se[threadIdx.x + w];
-      sb[threadIdx.x] += sb[threadIdx.x + w];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[0] = RedPartial{sm[0], se[0], sb[0], 0.0};
-}
-
 // Stored populations <-> dense FP32 planes (13 x nr x nx, no pitch).
 template <class C>
 __global__ void decode_kernel(const JetDesc *__restrict__ dp, int64_t step, int32_t view,
@@ -775,13 +706,6 @@ __global__ void encode_kernel(const JetDesc *__restrict__ dp, int64_t step, int3
   if (i >= d.nx) return;
   state_view<C>(d, view).put(d, p, i, j, in[((int64_t)p * d.nr + j) * d.nx + i],
                             plane_key(sr_key(i, j, step), p));
-}
-
-// Plain streaming copy, 16 B per lane per iteration.
-__global__ __launch_bounds__(256) void copy_kernel(const float4 *__restrict__ src,
-                                                   float4 *__restrict__ dst, int64_t n) {
-  for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < n; q += (int64_t)gridDim.x * 256)
-    dst[q] = src[q];
 }
 
 }  // namespace lbmx

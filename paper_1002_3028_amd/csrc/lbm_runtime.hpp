@@ -7,6 +7,7 @@
 #include <cmath>
 #include <cstdint>
 #include <cstring>
+#include <utility>
 #include <vector>
 
 #include "../../include/lbm.h"
@@ -53,31 +54,39 @@ int make_inlet(const lbm_config *c, int32_t n_t, const double *ux, const double 
 // ---- kernel tables ---------------------------------------------------------
 // A launch variant: block (bx, by), tile (bx * nx) x (by * ny) nodes, the
 // occupancy target, the cache policy, and the steps one launch advances
-// (2: the LDS-blocked two-step kernel).
+// (2: the LDS-blocked two-step kernel; more: the marching kernel, with
+// strips of 64 - 2 (steps - 1) columns and by tiles of march_rows() rows).
 struct TileShape {
   int bx, by, ny, nx, waves, cache, steps, lds;
   const void *fn[4];  // FP32, FP16-dev, BF16-dev, FP16-dev rounded stochastically
+  const void *big[4]; // the marching kernel's instances for larger property tables
 };
 const TileShape *tile_shapes(int *count);
-int default_tile_shape(int prec);
+extern const TileShape kMarch4;
+// The shape of a launch over `nodes` nodes of one storage form.
+int default_tile_shape(int prec, int64_t nodes);
+inline bool marches(const TileShape &s) { return s.big[0] != nullptr; }
 
 inline int codec_index(int prec) { return prec - LBM_PREC_FP32; }
 
 // One launch of tile shape `shape`: the step (or pair) at step0 + koff, with
-// `tog` the parity of two-step launches since the last advance and nsteps
-// (1 or 2) the steps a two-step kernel may take.
-int launch_step(int shape, int prec, int grid, hipStream_t st, const JetDesc *jets,
+// `tog` the parity of flip toggles since the last advance and nsteps the
+// steps it may take (at most the shape's); big_table: a jet's property table
+// has more entries than the marching kernel holds in LDS.
+int launch_step(int shape, int prec, bool big_table, int grid, hipStream_t st, const JetDesc *jets,
                 const int32_t *tiles, const BatchHdr *hdr, int32_t koff, int32_t tog,
                 int32_t nsteps, int32_t *flags);
-// Advance after a group of delta steps whose first npair launches were
-// two-step launches.
+// Advance after a group of delta steps in launches of spl steps and one of
+// the rest (spl = 0: one jet, its flip toggled by `flip`).
 int launch_advance(hipStream_t st, JetDesc *jets, const BatchHdr *hdr, int32_t njets_max,
-                   int32_t delta, int32_t npair);
+                   int32_t delta, int32_t spl, int32_t flip = 0);
 // Single-buffer step over shape 0's tile list.
 int launch_aa_step(int prec, int grid, hipStream_t st, const JetDesc *jets, const int32_t *tiles,
                    const BatchHdr *hdr, int32_t koff, int32_t *flags);
 // Helpers on the state after `step` steps, seen through `view`
 // (state_view_of).
+// Inlet entries (ux, ur, T) on the device, made the populations that enter.
+int launch_inlet(hipStream_t st, float4 *rows, size_t n);
 int launch_init(int prec, hipStream_t st, const JetDesc *d, const lbm_config *c, int64_t step,
                 int32_t view, const float4 *state, float4 u0);
 int launch_ghost_fill(int prec, hipStream_t st, const JetDesc *d, const lbm_config *c,
@@ -93,7 +102,13 @@ int launch_decode(int prec, hipStream_t st, const JetDesc *d, const lbm_config *
 int launch_encode(int prec, hipStream_t st, const JetDesc *d, const lbm_config *c, int64_t step,
                   int32_t view, const float *in);
 
-int tiles_of(const lbm_config *c, int shape, int32_t *tiles_x);
+// Tiles of a jet, per row in *tiles_x; rows: the marching kernel's tile_rows.
+int tiles_of(int32_t nx, int32_t nr, int shape, int32_t rows, int32_t *tiles_x);
+// Rows of a wave's tile for jets (nx, nr) marched in one launch.
+typedef std::vector<std::pair<int32_t, int32_t>> MarchJets;
+int32_t march_rows(const MarchJets &jets, int shape);
+int device_cus();  // of the current device
+bool big_table(const lbm_config *c);
 
 // Workgroups of the step kernel of `shape` (or of the single-buffer kernel)
 // that the current device holds at once: one full wave of a persistent grid.
