@@ -160,6 +160,57 @@ __device__ __forceinline__ void march_edges(const JetDesc &d, const MarchEdge<C>
   }
 }
 
+__device__ __forceinline__ float uniform(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+}
+__device__ __forceinline__ float lane_value(float v, int l) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
+}
+
+// A level's row f, g takes its place among the rows kept for the next level.
+__device__ __forceinline__ void march_keep(LevelRows &v, const float (&f)[9], const float (&g)[4],
+                                           const float (&up)[4]) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) v.u2[k] = v.u1[k], v.u1[k] = up[k];
+  v.h[0] = f[0];
+  v.h[1] = f[1];
+  v.h[2] = f[3];
+  v.h[3] = g[0];
+  v.h[4] = g[2];
+}
+
+// The same, and f, g become what the next level pulls at the row below: its
+// populations that move down with those of the kept rows.
+__device__ __forceinline__ void march_pull(LevelRows &v, float (&f)[9], float (&g)[4],
+                                           const float (&up)[4]) {
+  const LevelRows o = v;
+  march_keep(v, f, g, up);
+  f[0] = o.h[0];
+  f[1] = from_left(o.h[1]);
+  f[2] = o.u2[0];
+  f[3] = from_right(o.h[2]);
+  f[5] = from_left(o.u2[1]);
+  f[6] = from_right(o.u2[2]);
+  f[7] = from_right(f[7]);
+  f[8] = from_left(f[8]);
+  g[0] = from_left(o.h[3]);
+  g[1] = o.u2[3];
+  g[2] = from_right(o.h[4]);
+}
+
+template <int N>
+struct Int {
+  static constexpr int value = N;
+};
+// f(Int<1>()), f(Int<2>()), .. f(Int<K - 1>())
+template <int K, int N = 1, class F>
+__device__ __forceinline__ void below(const F &f) {
+  if constexpr (N < K) {
+    f(Int<N>());
+    below<K, N + 1>(f);
+  }
+}
+
 // Where a strip's ghost columns lie: none, column -1 with an inlet, column nx
 // with an outflow (the jet's two edges, whose rows cost little more than an
 // inner strip's), or any other rule or both.
