@@ -211,8 +211,8 @@ int lbm_set_populations(lbm_handle *h, const double *f, const double *g,
 int lbm_conservation(lbm_handle *h, double *mass3d, double *energy3d);
 /* lbm_conservation for callers that cannot allocate device memory (a
  * serving loop or harness that forbids allocation): the same reduction, with
- * the same kernels and the same bits, but its partial sums (at most 1025 of
- * 32 B: one per reduction workgroup and the total) live in a fixed array
+ * the same kernels and the same bits, but its partial sums (at most 1024 of
+ * 32 B, one per reduction workgroup) live in a fixed array
  * that the library holds on each device until the process ends, instead of
  * a buffer it allocates on first use.  Calls no allocating routine.  Every
  * call on one device uses that device's array: calls that overlap on one

@@ -18,12 +18,23 @@ constexpr int kMaxRedBlocks = 1024;
 }  // namespace
 
 // Partial sums of the no-allocation FP64 conservation reduction
-// (lbm_conservation_noalloc): one per reduction workgroup, then the total.
-// 32.8 KB.  Each device holds its own copy until the process ends.  In host
+// (lbm_conservation_noalloc): one per reduction workgroup.  32 KB.  Each device holds its own copy until the process ends.  In host
 // code the name stands for no device address: host code reaches the array
 // only through the pointer that hipGetSymbolAddress returns for the current
 // device (scratch_on).
-static __device__ __align__(256) RedPartial scratch[kMaxRedBlocks + 1];
+static __device__ __align__(256) RedPartial scratch[kMaxRedBlocks];
+
+namespace {
+// The handle's small results, in pinned host memory that kernels write to
+// directly; the profiles (2 (nx + nr) doubles) follow.
+struct HostBlock {
+  RedPartial total;   // of the conservation reduction
+  int32_t unstable;   // the steps' instability flag
+  int32_t bad_input;  // a value handed in was not finite
+};
+constexpr size_t kProfilesAt = 256;
+static_assert(sizeof(HostBlock) <= kProfilesAt, "host block");
+}  // namespace
 
 struct lbm_handle {
   int device = 0;
@@ -37,10 +48,12 @@ struct lbm_handle {
   bool own_stream = false;
   // device arrays
   JetDesc *d_desc = nullptr;
-  int32_t *d_flag = nullptr;
+  int32_t *d_flag = nullptr;  // host->unstable
   float4 *d_table = nullptr;
   float4 *d_inlet = nullptr;
-  Scratch scratch;
+  Scratch scratch, piece;
+  HostBlock *host = nullptr;
+  Pinned result;  // fields and populations of up to PINNED_RESULT bytes
   JetDesc desc{};
   int64_t step = 0;  // steps done
   int32_t flip = 0;  // state after s steps in buf[(s + flip) & 1]
@@ -99,15 +112,13 @@ void drop_graph(lbm_handle *h) {
 int sync_and_check(lbm_handle *h) {
   LBM_HIP(hipStreamSynchronize(h->stream));
   LBM_HIP(hipGetLastError());
-  int32_t flag = 0;
-  LBM_HIP(hipMemcpy(&flag, h->d_flag, sizeof flag, hipMemcpyDeviceToHost));
-  if (flag) h->unstable = true;
+  if (h->host->unstable) h->unstable = true;
   return h->unstable ? LBM_EUNSTABLE : LBM_OK;
 }
 
+// (the caller has synchronised the stream)
 int clear_flag(lbm_handle *h) {
-  const int32_t zero = 0;
-  LBM_HIP(hipMemcpy(h->d_flag, &zero, sizeof zero, hipMemcpyHostToDevice));
+  h->host->unstable = 0;
   h->unstable = false;
   return LBM_OK;
 }
@@ -117,8 +128,10 @@ void release(lbm_handle *h) {
   if (h->stream) (void)hipStreamSynchronize(h->stream);
   drop_graph(h);
   h->scratch.release();
+  h->piece.release();
+  h->result.release();
+  if (h->host) (void)hipHostFree(h->host);
   if (h->d_desc) (void)hipFree(h->d_desc);
-  if (h->d_flag) (void)hipFree(h->d_flag);
   if (h->d_table) (void)hipFree(h->d_table);
   if (h->d_inlet) (void)hipFree(h->d_inlet);
   if (h->own_buf && h->buf) (void)hipFree(h->buf);
@@ -192,16 +205,17 @@ int create_common(const lbm_config *cfg, void *dev_buf, size_t bytes, void *stre
   }
   std::vector<float4> table = make_table(&h->cfg);
   bool ok = hipMalloc(&h->d_desc, sizeof(JetDesc)) == hipSuccess &&
-            hipMalloc(&h->d_flag, sizeof(int32_t)) == hipSuccess &&
+            hipHostMalloc((void **)&h->host, kProfilesAt + 2 * sizeof(double) * ((size_t)cfg->nx + cfg->nr),
+                          hipHostMallocDefault) == hipSuccess &&
+            hipHostGetDevicePointer((void **)&h->d_flag, &h->host->unstable, 0) == hipSuccess &&
             hipMalloc(&h->d_table, table.size() * sizeof(float4)) == hipSuccess;
   if (!ok) {
     release(h);
     return LBM_ENOMEM;
   }
-  const int32_t zero = 0;
+  *h->host = HostBlock{};
   ok = hipMemcpy(h->d_table, table.data(), table.size() * sizeof(float4),
-                 hipMemcpyHostToDevice) == hipSuccess &&
-       hipMemcpy(h->d_flag, &zero, sizeof zero, hipMemcpyHostToDevice) == hipSuccess;
+                 hipMemcpyHostToDevice) == hipSuccess;
   if (!ok) {
     release(h);
     return LBM_EDEVICE;
@@ -395,19 +409,18 @@ int red_blocks(const lbm_handle *h) {
   return (int)std::min<int64_t>(kMaxRedBlocks, (nodes + RED_THREADS - 1) / RED_THREADS);
 }
 
-// Both conservation entry points: reduce into `part` (nblocks partials and
-// the total after them), wait, read the total back.
+// Both conservation entry points: reduce into `part` (nblocks partials), the
+// total into the host block, and wait.
 int conservation_into(lbm_handle *h, RedPartial *part, int nblocks, double *mass3d,
                       double *energy3d) {
   const int64_t nodes = (int64_t)h->cfg.nx * h->cfg.nr;
   int rc;
   if ((rc = launch_conservation(h->prec, h->stream, h->d_desc, nodes, h->step,
-                                view_of(h, h->step), part, nblocks, part + nblocks)))
+                                view_of(h, h->step), part, nblocks, &h->host->total)))
     return rc;
   const int st = sync_and_check(h);
   if (st == LBM_EDEVICE) return st;
-  RedPartial r;
-  LBM_HIP(hipMemcpy(&r, part + nblocks, sizeof r, hipMemcpyDeviceToHost));
+  const RedPartial r = h->host->total;
   *mass3d = r.mass;
   *energy3d = r.energy;
   if (r.bad != 0.0) h->unstable = true;
@@ -482,51 +495,53 @@ int lbm_set_tile_shape(lbm_handle *h, int32_t index) {
 
 int lbm_moments(lbm_handle *h, double *rho, double *ux, double *ur, double *T) {
   if (!h) return LBM_EINVAL;
-  const int64_t nodes = (int64_t)h->cfg.nx * h->cfg.nr;
+  const int64_t nx = h->cfg.nx, nodes = nx * h->cfg.nr;
+  double *const to[4] = {rho, ux, ur, T};
+  const int32_t view = view_of(h, h->step);
+  int rc;
   void *p;
-  int rc = h->scratch.get(nodes * sizeof(float4), &p);
-  if (rc) return rc;
-  if ((rc = launch_moments(h->prec, h->stream, h->d_desc, &h->cfg, h->step, view_of(h, h->step),
-                             (float4 *)p)))
-    return rc;
-  const int st = sync_and_check(h);
-  if (st == LBM_EDEVICE) return st;
-  std::vector<float4> m((size_t)nodes);
-  LBM_HIP(hipMemcpy(m.data(), p, nodes * sizeof(float4), hipMemcpyDeviceToHost));
-  bool finite = true;
-  for (int64_t n = 0; n < nodes; ++n) {
-    if (rho) rho[n] = m[n].x;
-    if (ux) ux[n] = m[n].y;
-    if (ur) ur[n] = m[n].z;
-    if (T) T[n] = m[n].w;
-    finite = finite && std::isfinite(m[n].x) && std::isfinite(m[n].w) && m[n].x > 0.f;
+  if (4 * nodes * sizeof(double) <= PINNED_RESULT) {
+    if ((rc = h->result.get(4 * nodes * sizeof(double), &p))) return rc;
+    if ((rc = launch_moments(h->prec, h->stream, h->d_desc, &h->cfg, h->step, view, 0, h->cfg.nr,
+                             (double *)p, nodes, h->d_flag)))
+      return rc;
+    const int st = sync_and_check(h);
+    if (st == LBM_EDEVICE) return st;
+    for (int q = 0; q < 4; ++q)
+      if (to[q]) std::memcpy(to[q], (double *)p + q * nodes, nodes * sizeof(double));
+    return st;
   }
-  if (!finite) h->unstable = true;
-  return h->unstable ? LBM_EUNSTABLE : LBM_OK;
+  const int32_t rows = (int32_t)std::min<int64_t>(
+      h->cfg.nr, std::max<int64_t>(1, (int64_t)PIECE_BYTES / (4 * nx * (int64_t)sizeof(double))));
+  if ((rc = h->piece.get(4 * nx * rows * sizeof(double), &p))) return rc;
+  for (int32_t j0 = 0; j0 < h->cfg.nr; j0 += rows) {
+    const int32_t n = std::min(rows, h->cfg.nr - j0);
+    if ((rc = launch_moments(h->prec, h->stream, h->d_desc, &h->cfg, h->step, view, j0, n,
+                             (double *)p, nx * n, h->d_flag)))
+      return rc;
+    LBM_HIP(hipStreamSynchronize(h->stream));
+    for (int q = 0; q < 4; ++q)
+      if (to[q])
+        LBM_HIP(hipMemcpy(to[q] + nx * j0, (double *)p + q * nx * n, nx * n * sizeof(double),
+                          hipMemcpyDeviceToHost));
+  }
+  return sync_and_check(h);
 }
 
 int lbm_profiles(lbm_handle *h, double *ux_axis, double *T_axis, double *ux_exit,
                  double *T_exit) {
   if (!h) return LBM_EINVAL;
-  const int n = h->cfg.nx + h->cfg.nr;
-  void *p;
-  int rc = h->scratch.get(n * sizeof(float2), &p);
+  const size_t nx = h->cfg.nx, nr = h->cfg.nr;
+  const double *p = (const double *)((char *)h->host + kProfilesAt);
+  const int rc = launch_profiles(h->prec, h->stream, h->d_desc, &h->cfg, h->step,
+                                 view_of(h, h->step), (double *)p);
   if (rc) return rc;
-  if ((rc = launch_profiles(h->prec, h->stream, h->d_desc, &h->cfg, h->step, view_of(h, h->step),
-                              (float2 *)p)))
-    return rc;
   const int st = sync_and_check(h);
   if (st == LBM_EDEVICE) return st;
-  std::vector<float2> v(n);
-  LBM_HIP(hipMemcpy(v.data(), p, n * sizeof(float2), hipMemcpyDeviceToHost));
-  for (int i = 0; i < h->cfg.nx; ++i) {
-    if (ux_axis) ux_axis[i] = v[i].x;
-    if (T_axis) T_axis[i] = v[i].y;
-  }
-  for (int j = 0; j < h->cfg.nr; ++j) {
-    if (ux_exit) ux_exit[j] = v[h->cfg.nx + j].x;
-    if (T_exit) T_exit[j] = v[h->cfg.nx + j].y;
-  }
+  if (ux_axis) std::memcpy(ux_axis, p, nx * sizeof(double));
+  if (T_axis) std::memcpy(T_axis, p + nx, nx * sizeof(double));
+  if (ux_exit) std::memcpy(ux_exit, p + 2 * nx, nr * sizeof(double));
+  if (T_exit) std::memcpy(T_exit, p + 2 * nx + nr, nr * sizeof(double));
   return st;
 }
 
@@ -534,7 +549,7 @@ int lbm_conservation(lbm_handle *h, double *mass3d, double *energy3d) {
   if (!h || !mass3d || !energy3d) return LBM_EINVAL;
   const int nblocks = red_blocks(h);
   void *p;
-  const int rc = h->scratch.get((nblocks + 1) * sizeof(RedPartial), &p);
+  const int rc = h->scratch.get(nblocks * sizeof(RedPartial), &p);
   if (rc) return rc;
   return conservation_into(h, (RedPartial *)p, nblocks, mass3d, energy3d);
 }
@@ -576,45 +591,81 @@ int lbm_set_state(lbm_handle *h, const double *rho, const double *ux, const doub
 int lbm_get_populations(lbm_handle *h, double *f, double *g) {
   if (!h) return LBM_EINVAL;
   const int64_t nodes = (int64_t)h->cfg.nx * h->cfg.nr;
+  const size_t one = nodes * sizeof(double);
+  const int32_t view = view_of(h, h->step);
+  int rc;
   void *p;
-  int rc = h->scratch.get(NPOP * nodes * sizeof(float), &p);
-  if (rc) return rc;
-  if ((rc = launch_decode(h->prec, h->stream, h->d_desc, &h->cfg, h->step, view_of(h, h->step),
-                           (float *)p)))
-    return rc;
-  const int st = sync_and_check(h);
-  if (st == LBM_EDEVICE) return st;
-  std::vector<float> v((size_t)(NPOP * nodes));
-  LBM_HIP(hipMemcpy(v.data(), p, v.size() * sizeof(float), hipMemcpyDeviceToHost));
-  for (int64_t q = 0; q < 9 * nodes; ++q)
-    if (f) f[q] = v[q];
-  for (int64_t q = 0; q < 4 * nodes; ++q)
-    if (g) g[q] = v[9 * nodes + q];
-  return st;
+  if (NPOP * one <= PINNED_RESULT) {
+    if ((rc = h->result.get(NPOP * one, &p))) return rc;
+    if ((rc = launch_decode(h->prec, h->stream, h->d_desc, &h->cfg, h->step, view, 0, NPOP,
+                            (double *)p)))
+      return rc;
+    const int st = sync_and_check(h);
+    if (st == LBM_EDEVICE) return st;
+    if (f) std::memcpy(f, p, 9 * one);
+    if (g) std::memcpy(g, (double *)p + 9 * nodes, 4 * one);
+    return st;
+  }
+  const int planes = (int)std::min<size_t>(NPOP, std::max<size_t>(1, PIECE_BYTES / one));
+  if ((rc = h->piece.get(planes * one, &p))) return rc;
+  for (int q0 = 0; q0 < NPOP; q0 += planes) {
+    const int n = std::min(planes, NPOP - q0);
+    if ((rc = launch_decode(h->prec, h->stream, h->d_desc, &h->cfg, h->step, view, q0, n,
+                            (double *)p)))
+      return rc;
+    LBM_HIP(hipStreamSynchronize(h->stream));
+    // (planes of one array follow each other in it: one copy)
+    const int nf = std::max(0, std::min(9, q0 + n) - q0);
+    if (nf > 0 && f)
+      LBM_HIP(hipMemcpy(f + q0 * nodes, p, nf * one, hipMemcpyDeviceToHost));
+    if (n > nf && g)
+      LBM_HIP(hipMemcpy(g + (q0 + nf - 9) * nodes, (double *)p + nf * nodes, (n - nf) * one,
+                        hipMemcpyDeviceToHost));
+  }
+  return sync_and_check(h);
 }
 
 int lbm_set_populations(lbm_handle *h, const double *f, const double *g, int64_t step) {
   if (!h || !f || !g || step < 0) return LBM_EINVAL;
   const int64_t nodes = (int64_t)h->cfg.nx * h->cfg.nr;
-  std::vector<float> v((size_t)(NPOP * nodes));
-  for (int64_t q = 0; q < 9 * nodes; ++q) {
-    if (!std::isfinite(f[q])) return LBM_EINVAL;
-    v[q] = (float)f[q];
-  }
-  for (int64_t q = 0; q < 4 * nodes; ++q) {
-    if (!std::isfinite(g[q])) return LBM_EINVAL;
-    v[9 * nodes + q] = (float)g[q];
-  }
-  void *p;
-  int rc = h->scratch.get(v.size() * sizeof(float), &p);
+  const size_t one = nodes * sizeof(double);
+  // the values as floats in device memory, checked on the way; the state is
+  // touched only if all are finite
+  void *v, *p;
+  int rc = h->scratch.get(NPOP * nodes * sizeof(float), &v);
   if (rc) return rc;
   LBM_HIP(hipStreamSynchronize(h->stream));
-  LBM_HIP(hipMemcpy(p, v.data(), v.size() * sizeof(float), hipMemcpyHostToDevice));
+  h->host->bad_input = 0;
+  if (NPOP * one <= PINNED_RESULT) {
+    if ((rc = h->result.get(NPOP * one, &p))) return rc;
+    std::memcpy(p, f, 9 * one);
+    std::memcpy((double *)p + 9 * nodes, g, 4 * one);
+    if ((rc = launch_narrow(h->stream, (const double *)p, (float *)v, NPOP * nodes,
+                            &h->host->bad_input)))
+      return rc;
+  } else {
+    const int planes = (int)std::min<size_t>(NPOP, std::max<size_t>(1, PIECE_BYTES / one));
+    if ((rc = h->piece.get(planes * one, &p))) return rc;
+    for (int q0 = 0; q0 < NPOP; q0 += planes) {
+      const int n = std::min(planes, NPOP - q0);
+      const int nf = std::max(0, std::min(9, q0 + n) - q0);
+      LBM_HIP(hipStreamSynchronize(h->stream));  // (the last piece has been read)
+      if (nf > 0) LBM_HIP(hipMemcpy(p, f + q0 * nodes, nf * one, hipMemcpyHostToDevice));
+      if (n > nf)
+        LBM_HIP(hipMemcpy((double *)p + nf * nodes, g + (q0 + nf - 9) * nodes, (n - nf) * one,
+                          hipMemcpyHostToDevice));
+      if ((rc = launch_narrow(h->stream, (const double *)p, (float *)v + q0 * nodes, n * nodes,
+                              &h->host->bad_input)))
+        return rc;
+    }
+  }
+  LBM_HIP(hipStreamSynchronize(h->stream));
+  if (h->host->bad_input) return LBM_EINVAL;
   h->step = step;
   h->base = step;
   if ((rc = upload_desc(h))) return rc;
   if ((rc = launch_encode(h->prec, h->stream, h->d_desc, &h->cfg, step, view_of(h, step),
-                           (const float *)p)))
+                           (const float *)v)))
     return rc;
   if ((rc = launch_ghost_fill(h->prec, h->stream, h->d_desc, &h->cfg, step, view_of(h, step)))) return rc;
   LBM_HIP(hipStreamSynchronize(h->stream));

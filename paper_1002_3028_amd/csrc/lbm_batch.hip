@@ -139,12 +139,20 @@ struct lbm_batch {
   hipStream_t io = nullptr;        // profile and moment extraction
   hipStream_t cap = nullptr;       // graph capture (never holds work)
   hipEvent_t mark = nullptr;       // "everything enqueued so far" on `stream`
+  // work put on `stream` (groups and admissions), how much of it the
+  // extraction stream has been told to wait for, and how much the host has
+  // seen complete.  An extraction after that needs no event: recording one on
+  // a stream and making another wait for it took 45 of the 65 us of a
+  // running jet's profiles.
+  int64_t queued = 0, io_asked = 0, io_seen = 0;
   JetDesc *h_slot = nullptr;       // pinned staging of each slot's descriptor
-  int32_t *h_zero = nullptr;       // pinned 0 (a slot's instability flag)
   // 0: one cohort.  Two cohorts run at once (two streams), and together they
   // fill the 256 MiB Infinity Cache.
   size_t cohort_bytes = size_t(128) << 20;
-  int32_t *d_flags = nullptr;
+  // instability flags, one per slot, in pinned host memory (a step writes one
+  // only when a jet has gone bad; the host reads it after the jet's results)
+  int32_t *h_flags = nullptr, *d_flags = nullptr;
+  Pinned result;                   // profiles and small fields, written by kernels
   // pinned staging of what rebuild uploads (cohort after cohort, compact), so
   // that the uploads are asynchronous copies ordered before the launches; two
   // copies, as the device lists
@@ -368,11 +376,13 @@ int run_group(lbm_batch *b, int32_t k, int32_t c, hipStream_t st) {
 // in which its jet reached its target, or, for a jet still running, all the
 // work enqueued so far.
 int io_after(lbm_batch *b, const Slot &sl) {
+  if (b->io_seen == b->queued) return LBM_OK;
   if (sl.done_seq >= 0) {
     LBM_HIP(hipStreamWaitEvent(b->io, b->done[sl.done_seq % lbm_batch::RING], 0));
   } else {
     LBM_HIP(hipEventRecord(b->mark, b->stream));
     LBM_HIP(hipStreamWaitEvent(b->io, b->mark, 0));
+    b->io_asked = b->queued;
   }
   return LBM_OK;
 }
@@ -408,7 +418,9 @@ int lbm_batch_create(size_t budget_bytes, int32_t max_slots, int32_t precision,
             hipMalloc(&b->d_slot_desc, max_slots * sizeof(JetDesc)) == hipSuccess &&
             hipMalloc(&b->d_tiles, 2 * mc * (max_slots + 1) * sizeof(int32_t)) == hipSuccess &&
             hipMalloc(&b->d_hdr, 2 * mc * sizeof(BatchHdr)) == hipSuccess &&
-            hipMalloc(&b->d_flags, max_slots * sizeof(int32_t)) == hipSuccess &&
+            hipHostMalloc((void **)&b->h_flags, max_slots * sizeof(int32_t),
+                          hipHostMallocDefault) == hipSuccess &&
+            hipHostGetDevicePointer((void **)&b->d_flags, b->h_flags, 0) == hipSuccess &&
             hipHostMalloc(&b->h_jets, 2 * max_slots * sizeof(JetDesc), hipHostMallocDefault) ==
                 hipSuccess &&
             hipHostMalloc(&b->h_tiles, 2 * (max_slots + mc) * sizeof(int32_t),
@@ -416,8 +428,9 @@ int lbm_batch_create(size_t budget_bytes, int32_t max_slots, int32_t precision,
             hipHostMalloc(&b->h_hdr, 2 * mc * sizeof(BatchHdr), hipHostMallocDefault) ==
                 hipSuccess &&
             hipHostMalloc(&b->h_slot, max_slots * sizeof(JetDesc), hipHostMallocDefault) ==
-                hipSuccess &&
-            hipHostMalloc(&b->h_zero, sizeof(int32_t), hipHostMallocDefault) == hipSuccess;
+                hipSuccess;
+  void *first;  // (the profiles of jets of up to 4096 columns and rows)
+  ok = ok && b->result.get(size_t(64) << 10, &first) == LBM_OK;
   const size_t pooled = (size_t)std::min(max_slots, kPoolSlots);
   ok = ok && hipMalloc(&b->pool_d, pooled * kBlockBytes) == hipSuccess &&
        hipHostMalloc(&b->pool_h, pooled * kBlockBytes, hipHostMallocDefault) == hipSuccess;
@@ -448,13 +461,10 @@ int lbm_batch_create(size_t budget_bytes, int32_t max_slots, int32_t precision,
     ok = hipEventCreateWithFlags(&b->done[q], hipEventDefault) == hipSuccess &&
          hipEventCreateWithFlags(&b->start[q], hipEventDefault) == hipSuccess;
   if (ok) {
-    *b->h_zero = 0;
-    std::vector<int32_t> zeros(max_slots, 0);
+    std::memset(b->h_flags, 0, max_slots * sizeof(int32_t));
     std::vector<BatchHdr> hz(2 * mc, BatchHdr{0, 0, {0, 0}});
     std::vector<int32_t> tz(2 * mc * (max_slots + 1), 0);
-    ok = hipMemcpy(b->d_flags, zeros.data(), max_slots * sizeof(int32_t),
-                   hipMemcpyHostToDevice) == hipSuccess &&
-         hipMemcpy(b->d_hdr, hz.data(), hz.size() * sizeof(BatchHdr), hipMemcpyHostToDevice) ==
+    ok = hipMemcpy(b->d_hdr, hz.data(), hz.size() * sizeof(BatchHdr), hipMemcpyHostToDevice) ==
              hipSuccess &&
          hipMemcpy(b->d_tiles, tz.data(), tz.size() * sizeof(int32_t), hipMemcpyHostToDevice) ==
              hipSuccess;
@@ -571,11 +581,13 @@ int lbm_batch_admit(lbm_batch *b, const lbm_config *cfg, int32_t n_t, const doub
   b->h_slot[s] = d;
   std::memcpy(blk.h, table.data(), table.size() * sizeof(float4));
   std::memcpy((char *)blk.h + tb, rows.data(), rows.size() * sizeof(float4));
+  ++b->queued;
   LBM_HIP(hipMemcpyAsync(blk.p, blk.h, tb + ib, hipMemcpyHostToDevice, b->stream));
   LBM_HIP(hipMemcpyAsync(b->d_slot_desc + s, b->h_slot + s, sizeof(JetDesc),
                          hipMemcpyHostToDevice, b->stream));
-  LBM_HIP(hipMemcpyAsync(b->d_flags + s, b->h_zero, sizeof(int32_t), hipMemcpyHostToDevice,
-                         b->stream));
+  // (no step of an earlier jet writes the flag any more, and this one's come
+  // behind)
+  b->h_flags[s] = 0;
   if ((rc = launch_inlet(b->stream, sl.d_inlet, rows.size()))) return rc;
   const float4 u0 =
       make_float4((float)cfg->rho0, (float)cfg->ux0, (float)cfg->ur0, (float)cfg->T0);
@@ -597,6 +609,7 @@ int lbm_batch_run(lbm_batch *b, int32_t k_steps) {
   int rc;
   if (b->dirty && (rc = rebuild(b))) return rc;
   if (b->active.empty()) return LBM_OK;
+  ++b->queued;
   LBM_HIP(hipEventRecord(b->start[b->seq % lbm_batch::RING], b->stream));
   const int32_t ns = std::max(1, std::min(b->nstreams, b->n_cohorts));
   if (ns > 1) {
@@ -673,15 +686,12 @@ int lbm_batch_poll(lbm_batch *b, int32_t slot, int64_t *steps_done) {
 
 // Extraction of one jet's results runs on the batch's extraction stream after
 // the group in which the jet finished (io_after), so that it waits neither
-// for the groups queued since nor holds them up: the helper kernel, then the
-// jet's instability flag and the result back to the host.
-static int extract(lbm_batch *b, int32_t slot, void *dev, size_t bytes, void *host,
-                   int32_t *flag) {
-  LBM_HIP(hipMemcpyAsync(flag, b->d_flags + slot, sizeof(int32_t), hipMemcpyDeviceToHost,
-                         b->io));
-  LBM_HIP(hipMemcpyAsync(host, dev, bytes, hipMemcpyDeviceToHost, b->io));
+// for the groups queued since nor holds them up: the helper kernel writes
+// them to pinned host memory (or, large fields, to device memory in pieces).
+static int extracted(lbm_batch *b) {
   LBM_HIP(hipStreamSynchronize(b->io));
   LBM_HIP(hipGetLastError());
+  b->io_seen = b->io_asked;
   return LBM_OK;
 }
 
@@ -689,50 +699,54 @@ int lbm_batch_profiles(lbm_batch *b, int32_t slot, double *ux_axis, double *T_ax
                        double *ux_exit, double *T_exit) {
   Slot *sl = slot_of(b, slot);
   if (!sl) return LBM_EINVAL;
-  const int n = sl->cfg.nx + sl->cfg.nr;
-  void *p;
-  int rc = b->scratch.get(n * sizeof(float2), &p);
+  const size_t nx = sl->cfg.nx, nr = sl->cfg.nr;
+  void *v;
+  int rc = b->result.get(2 * (nx + nr) * sizeof(double), &v);
   if (rc) return rc;
   if ((rc = io_after(b, *sl))) return rc;
   if ((rc = launch_profiles(sl->prec, b->io, b->d_slot_desc + slot, &sl->cfg, sl->step,
-                            state_view_of(b->layout, sl->step, sl->flip), (float2 *)p)))
+                            state_view_of(b->layout, sl->step, sl->flip), (double *)v)))
     return rc;
-  std::vector<float2> v(n);
-  int32_t flag = 0;
-  if ((rc = extract(b, slot, p, n * sizeof(float2), v.data(), &flag))) return rc;
-  for (int i = 0; i < sl->cfg.nx; ++i) {
-    if (ux_axis) ux_axis[i] = v[i].x;
-    if (T_axis) T_axis[i] = v[i].y;
-  }
-  for (int j = 0; j < sl->cfg.nr; ++j) {
-    if (ux_exit) ux_exit[j] = v[sl->cfg.nx + j].x;
-    if (T_exit) T_exit[j] = v[sl->cfg.nx + j].y;
-  }
-  return flag ? LBM_EUNSTABLE : LBM_OK;
+  if ((rc = extracted(b))) return rc;
+  const double *p = (const double *)v;
+  if (ux_axis) std::memcpy(ux_axis, p, nx * sizeof(double));
+  if (T_axis) std::memcpy(T_axis, p + nx, nx * sizeof(double));
+  if (ux_exit) std::memcpy(ux_exit, p + 2 * nx, nr * sizeof(double));
+  if (T_exit) std::memcpy(T_exit, p + 2 * nx + nr, nr * sizeof(double));
+  return b->h_flags[slot] ? LBM_EUNSTABLE : LBM_OK;
 }
 
 int lbm_batch_moments(lbm_batch *b, int32_t slot, double *rho, double *ux, double *ur,
                       double *T) {
   Slot *sl = slot_of(b, slot);
   if (!sl) return LBM_EINVAL;
-  const int64_t nodes = (int64_t)sl->cfg.nx * sl->cfg.nr;
-  void *p;
-  int rc = b->scratch.get(nodes * sizeof(float4), &p);
+  const int64_t nx = sl->cfg.nx, nr = sl->cfg.nr, nodes = nx * nr;
+  double *const to[4] = {rho, ux, ur, T};
+  const int32_t view = state_view_of(b->layout, sl->step, sl->flip);
+  const bool small = 4 * nodes * sizeof(double) <= PINNED_RESULT;
+  const int64_t rows =
+      small ? nr
+            : std::min<int64_t>(nr, std::max<int64_t>(1, (int64_t)PIECE_BYTES /
+                                                             (4 * nx * (int64_t)sizeof(double))));
+  void *v;
+  const size_t need = 4 * nx * rows * sizeof(double);
+  int rc = small ? b->result.get(need, &v) : b->scratch.get(need, &v);
   if (rc) return rc;
   if ((rc = io_after(b, *sl))) return rc;
-  if ((rc = launch_moments(sl->prec, b->io, b->d_slot_desc + slot, &sl->cfg, sl->step,
-                           state_view_of(b->layout, sl->step, sl->flip), (float4 *)p)))
-    return rc;
-  std::vector<float4> m((size_t)nodes);
-  int32_t flag = 0;
-  if ((rc = extract(b, slot, p, nodes * sizeof(float4), m.data(), &flag))) return rc;
-  for (int64_t n = 0; n < nodes; ++n) {
-    if (rho) rho[n] = m[n].x;
-    if (ux) ux[n] = m[n].y;
-    if (ur) ur[n] = m[n].z;
-    if (T) T[n] = m[n].w;
+  for (int64_t j0 = 0; j0 < nr; j0 += rows) {
+    const int64_t n = std::min(rows, nr - j0);
+    if ((rc = launch_moments(sl->prec, b->io, b->d_slot_desc + slot, &sl->cfg, sl->step, view,
+                             (int32_t)j0, (int32_t)n, (double *)v, nx * n, nullptr)))
+      return rc;
+    if ((rc = extracted(b))) return rc;
+    for (int q = 0; q < 4; ++q) {
+      const double *p = (const double *)v + q * nx * n;
+      if (!to[q]) continue;
+      if (small) std::memcpy(to[q] + nx * j0, p, nx * n * sizeof(double));
+      else LBM_HIP(hipMemcpy(to[q] + nx * j0, p, nx * n * sizeof(double), hipMemcpyDeviceToHost));
+    }
   }
-  return flag ? LBM_EUNSTABLE : LBM_OK;
+  return b->h_flags[slot] ? LBM_EUNSTABLE : LBM_OK;
 }
 
 int lbm_batch_retire(lbm_batch *b, int32_t slot) {
@@ -835,12 +849,12 @@ void lbm_batch_destroy(lbm_batch *b) {
   if (b->d_slot_desc) (void)hipFree(b->d_slot_desc);
   if (b->d_tiles) (void)hipFree(b->d_tiles);
   if (b->d_hdr) (void)hipFree(b->d_hdr);
-  if (b->d_flags) (void)hipFree(b->d_flags);
+  if (b->h_flags) (void)hipHostFree(b->h_flags);
+  b->result.release();
   if (b->h_jets) (void)hipHostFree(b->h_jets);
   if (b->h_tiles) (void)hipHostFree(b->h_tiles);
   if (b->h_hdr) (void)hipHostFree(b->h_hdr);
   if (b->h_slot) (void)hipHostFree(b->h_slot);
-  if (b->h_zero) (void)hipHostFree(b->h_zero);
   if (b->io) (void)hipStreamDestroy(b->io);
   if (b->cap) (void)hipStreamDestroy(b->cap);
   if (b->mark) (void)hipEventDestroy(b->mark);

@@ -64,6 +64,19 @@ __global__ __launch_bounds__(256) void copy_kernel(const float4 *__restrict__ sr
     dst[q] = src[q];
 }
 
+// Doubles as floats; *bad is set if one is not finite.
+__global__ __launch_bounds__(256) void narrow_kernel(const double *__restrict__ in,
+                                                     float *__restrict__ out, int64_t n,
+                                                     int32_t *__restrict__ bad) {
+  bool ok = true;
+  for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < n; q += (int64_t)gridDim.x * 256) {
+    const double v = in[q];
+    out[q] = (float)v;
+    ok &= fabs(v) < __builtin_inf();
+  }
+  if (!ok) *bad = 1;
+}
+
 // ---- validation (same rules the paper's setting implies: tau > 1/2 so that
 // nu, alpha > 0; Pr_t > 0; a symmetry axis only at r = 0) ------------------
 static bool side_ok(int side, int bc) {
@@ -380,30 +393,29 @@ int launch_ghost_fill(int prec, hipStream_t st, const JetDesc *d, const lbm_conf
   return LBM_OK;
 }
 
-template <class C>
-static void moments_t(hipStream_t st, const JetDesc *d, const lbm_config *c, int64_t step, int32_t view,
-                      float4 *out) {
-  hipLaunchKernelGGL(moments_kernel<C>, dim3((c->nx + 255) / 256, c->nr), dim3(256), 0, st, d,
-                     step, view, out);
-}
 int launch_moments(int prec, hipStream_t st, const JetDesc *d, const lbm_config *c,
-                   int64_t step, int32_t view, float4 *out) {
-  if (prec == LBM_PREC_FP32) moments_t<CodecF32>(st, d, c, step, view, out);
-  else if (prec == LBM_PREC_FP16DEV) moments_t<CodecF16>(st, d, c, step, view, out);
-  else if (prec == LBM_PREC_FP16SR) moments_t<CodecF16SR>(st, d, c, step, view, out);
-  else moments_t<CodecBF16>(st, d, c, step, view, out);
+                   int64_t step, int32_t view, int32_t j0, int32_t rows, double *out,
+                   int64_t stride, int32_t *flags) {
+  const auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((c->nx + 255) / 256, rows), dim3(256), 0, st, d, step, view,
+                       j0, out, stride, flags);
+  };
+  if (prec == LBM_PREC_FP32) go(moments_kernel<CodecF32>);
+  else if (prec == LBM_PREC_FP16DEV) go(moments_kernel<CodecF16>);
+  else if (prec == LBM_PREC_FP16SR) go(moments_kernel<CodecF16SR>);
+  else go(moments_kernel<CodecBF16>);
   LBM_HIP(hipGetLastError());
   return LBM_OK;
 }
 
 template <class C>
 static void profiles_t(hipStream_t st, const JetDesc *d, const lbm_config *c, int64_t step, int32_t view,
-                       float2 *out) {
+                       double *out) {
   const int n = c->nx + c->nr;
   hipLaunchKernelGGL(profiles_kernel<C>, dim3((n + 255) / 256), dim3(256), 0, st, d, step, view, out);
 }
 int launch_profiles(int prec, hipStream_t st, const JetDesc *d, const lbm_config *c,
-                    int64_t step, int32_t view, float2 *out) {
+                    int64_t step, int32_t view, double *out) {
   if (prec == LBM_PREC_FP32) profiles_t<CodecF32>(st, d, c, step, view, out);
   else if (prec == LBM_PREC_FP16DEV) profiles_t<CodecF16>(st, d, c, step, view, out);
   else if (prec == LBM_PREC_FP16SR) profiles_t<CodecF16SR>(st, d, c, step, view, out);
@@ -432,18 +444,23 @@ int launch_conservation(int prec, hipStream_t st, const JetDesc *d, int64_t node
   return LBM_OK;
 }
 
-template <class C>
-static void decode_t(hipStream_t st, const JetDesc *d, const lbm_config *c, int64_t step, int32_t view,
-                     float *out) {
-  hipLaunchKernelGGL(decode_kernel<C>, dim3((c->nx + 255) / 256, c->nr, NPOP), dim3(256), 0, st,
-                     d, step, view, out);
+int launch_decode(int prec, hipStream_t st, const JetDesc *d, const lbm_config *c, int64_t step,
+                  int32_t view, int32_t p0, int32_t planes, double *out) {
+  const auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((c->nx + 255) / 256, c->nr, planes), dim3(256), 0, st, d, step,
+                       view, p0, out);
+  };
+  if (prec == LBM_PREC_FP32) go(decode_kernel<CodecF32>);
+  else if (prec == LBM_PREC_FP16DEV) go(decode_kernel<CodecF16>);
+  else if (prec == LBM_PREC_FP16SR) go(decode_kernel<CodecF16SR>);
+  else go(decode_kernel<CodecBF16>);
+  LBM_HIP(hipGetLastError());
+  return LBM_OK;
 }
-int launch_decode(int prec, hipStream_t st, const JetDesc *d, const lbm_config *c, int64_t step, int32_t view,
-                  float *out) {
-  if (prec == LBM_PREC_FP32) decode_t<CodecF32>(st, d, c, step, view, out);
-  else if (prec == LBM_PREC_FP16DEV) decode_t<CodecF16>(st, d, c, step, view, out);
-  else if (prec == LBM_PREC_FP16SR) decode_t<CodecF16SR>(st, d, c, step, view, out);
-  else decode_t<CodecBF16>(st, d, c, step, view, out);
+
+int launch_narrow(hipStream_t st, const double *in, float *out, int64_t n, int32_t *bad) {
+  const int blocks = (int)std::min<int64_t>((n + 255) / 256, 256 * 16);
+  hipLaunchKernelGGL(narrow_kernel, dim3(blocks), dim3(256), 0, st, in, out, n, bad);
   LBM_HIP(hipGetLastError());
   return LBM_OK;
 }

@@ -612,13 +612,16 @@ __global__ void init_kernel(const JetDesc *__restrict__ dp, int64_t step, int32_
     st.put(d, p, i, j, eq_plane(p, q.x, q.y, q.z, q.w), plane_key(key, p));
 }
 
-// Pre-collision moments (eq. 2) of the state after `step` steps:
-// float4 (rho, ux, ur, T) per node, i fastest.
+// Pre-collision moments (eq. 2) of the state after `step` steps, rows j0 to
+// j0 + gridDim.y - 1: four arrays of doubles (rho, ux, ur, T), i fastest,
+// `stride` apart, as the caller's arrays hold them.  flags (if given): set
+// where rho or T is not finite or rho <= 0.
 template <class C>
 __global__ void moments_kernel(const JetDesc *__restrict__ dp, int64_t step, int32_t view,
-                               float4 *__restrict__ out) {
+                               int32_t j0, double *__restrict__ out, int64_t stride,
+                               int32_t *__restrict__ flags) {
   const JetDesc &d = *dp;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x, j = blockIdx.y;
+  const int i = blockIdx.x * blockDim.x + threadIdx.x, j = j0 + (int)blockIdx.y;
   if (i >= d.nx) return;
   const State<C> s = state_view<C>(d, view);
   float f[9], g[4];
@@ -627,13 +630,20 @@ __global__ void moments_kernel(const JetDesc *__restrict__ dp, int64_t step, int
   const float mx = (f[1] + f[5] + f[8]) - (f[3] + f[6] + f[7]);
   const float mr = (f[2] + f[5] + f[6]) - (f[4] + f[7] + f[8]);
   const float T = (g[0] + g[1]) + (g[2] + g[3]);
-  out[(int64_t)j * d.nx + i] = make_float4(rho, mx / rho, mr / rho, T);
+  double *o = out + (int64_t)blockIdx.y * d.nx + i;
+  o[0] = rho;
+  o[stride] = mx / rho;
+  o[2 * stride] = mr / rho;
+  o[3 * stride] = T;
+  if (flags && !((rho > 0.0f) && (rho < __builtin_inff()) && (fabsf(T) < __builtin_inff())))
+    flags[d.slot] = 1;
 }
 
-// Centreline (j = 0) and exit column (i = nx-1): (ux, T) pairs, nx + nr.
+// Centreline (j = 0) and exit column (i = nx-1) as doubles: u_x and T of the
+// centreline (nx each), then of the exit column (nr each).
 template <class C>
 __global__ void profiles_kernel(const JetDesc *__restrict__ dp, int64_t step, int32_t view,
-                                float2 *__restrict__ out) {
+                                double *__restrict__ out) {
   const JetDesc &d = *dp;
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= d.nx + d.nr) return;
@@ -644,7 +654,9 @@ __global__ void profiles_kernel(const JetDesc *__restrict__ dp, int64_t step, in
   pulled_node<C>(d, s, i, j, f, g);
   const float rho = ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7])) + f[8];
   const float mx = (f[1] + f[5] + f[8]) - (f[3] + f[6] + f[7]);
-  out[t] = make_float2(mx / rho, (g[0] + g[1]) + (g[2] + g[3]));
+  double *o = t < d.nx ? out + i : out + 2 * (int64_t)d.nx + j;
+  o[0] = mx / rho;
+  o[t < d.nx ? d.nx : d.nr] = (g[0] + g[1]) + (g[2] + g[3]);
 }
 
 // FP64 conservation sums of the pre-collision moments: each workgroup takes
@@ -688,15 +700,18 @@ __global__ __launch_bounds__(RED_THREADS) void conservation_kernel(
   if (threadIdx.x == 0) partial[blockIdx.x] = RedPartial{sm[0], se[0], sb[0], 0.0};
 }
 
-// Stored populations <-> dense FP32 planes (13 x nr x nx, no pitch).
+// Stored populations p0 .. -> dense planes of doubles (nr x nx, no pitch).
 template <class C>
 __global__ void decode_kernel(const JetDesc *__restrict__ dp, int64_t step, int32_t view,
-                              float *__restrict__ out) {
+                              int32_t p0, double *__restrict__ out) {
   const JetDesc &d = *dp;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x, j = blockIdx.y, p = blockIdx.z;
+  const int i = blockIdx.x * blockDim.x + threadIdx.x, j = blockIdx.y;
+  const int p = p0 + (int)blockIdx.z;
   if (i >= d.nx) return;
-  out[((int64_t)p * d.nr + j) * d.nx + i] = state_view<C>(d, view).load(d, p, i, j);
+  out[((int64_t)blockIdx.z * d.nr + j) * d.nx + i] = state_view<C>(d, view).load(d, p, i, j);
 }
+
+// Dense FP32 planes (13 x nr x nx, no pitch) -> stored populations.
 
 template <class C>
 __global__ void encode_kernel(const JetDesc *__restrict__ dp, int64_t step, int32_t view,

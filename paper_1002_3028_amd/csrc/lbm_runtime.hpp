@@ -92,13 +92,15 @@ int launch_init(int prec, hipStream_t st, const JetDesc *d, const lbm_config *c,
 int launch_ghost_fill(int prec, hipStream_t st, const JetDesc *d, const lbm_config *c,
                       int64_t step, int32_t view);
 int launch_moments(int prec, hipStream_t st, const JetDesc *d, const lbm_config *c,
-                   int64_t step, int32_t view, float4 *out);
+                   int64_t step, int32_t view, int32_t j0, int32_t rows, double *out,
+                   int64_t stride, int32_t *flags);
 int launch_profiles(int prec, hipStream_t st, const JetDesc *d, const lbm_config *c,
-                    int64_t step, int32_t view, float2 *out);
+                    int64_t step, int32_t view, double *out);
 int launch_conservation(int prec, hipStream_t st, const JetDesc *d, int64_t nodes, int64_t step,
                         int32_t view, RedPartial *partial, int nblocks, RedPartial *out);
 int launch_decode(int prec, hipStream_t st, const JetDesc *d, const lbm_config *c, int64_t step,
-                  int32_t view, float *out);
+                  int32_t view, int32_t p0, int32_t planes, double *out);
+int launch_narrow(hipStream_t st, const double *in, float *out, int64_t n, int32_t *bad);
 int launch_encode(int prec, hipStream_t st, const JetDesc *d, const lbm_config *c, int64_t step,
                   int32_t view, const float *in);
 
@@ -113,6 +115,40 @@ bool big_table(const lbm_config *c);
 // Workgroups of the step kernel of `shape` (or of the single-buffer kernel)
 // that the current device holds at once: one full wave of a persistent grid.
 int resident_workgroups(int shape, int prec, bool single_buffer);
+
+// Results are written as the doubles the caller takes.  Up to PINNED_RESULT
+// bytes the kernel writes them straight into pinned host memory: one launch
+// and one wait (profiles of a 128 x 32 jet 20 us with the binding; device
+// memory, two copies back and a conversion on the host took 48).  Larger ones
+// go through device memory in pieces of PIECE_BYTES and are copied to the
+// caller's arrays at the copy engine's rate, with no pass over them on the
+// host (populations out and in and fields of a 1024 x 256 jet: 3.6 ms, with
+// host conversions 7.4).
+constexpr size_t PINNED_RESULT = size_t(1) << 20;
+constexpr size_t PIECE_BYTES = size_t(64) << 20;
+
+// Pinned host memory that kernels write to; grows on demand.
+struct Pinned {
+  void *p = nullptr;
+  size_t bytes = 0;
+  int get(size_t need, void **out) {
+    if (need > bytes) {
+      release();
+      if (hipHostMalloc(&p, need, hipHostMallocDefault) != hipSuccess) {
+        p = nullptr;
+        return LBM_ENOMEM;
+      }
+      bytes = need;
+    }
+    *out = p;
+    return LBM_OK;
+  }
+  void release() {
+    if (p) (void)hipHostFree(p);
+    p = nullptr;
+    bytes = 0;
+  }
+};
 
 // Simple device scratch that grows on demand.
 struct Scratch {

@@ -1,0 +1,73 @@
+"""Fields and populations out and in, at the sizes where the path changes:
+results of up to 1 MiB come through pinned memory, larger ones in pieces of
+64 MiB (rows of the fields, planes of the populations)."""
+import numpy as np
+import pytest
+
+from gpu_common import host_threads, rel_err, require_gpu, tiny_params
+
+pytestmark = pytest.mark.gpu
+
+# (nx, nr): populations of exactly 1 MiB or less and just more (10 082 nodes),
+# fields of exactly 1 MiB and just more (32 768 nodes), planes in several
+# pieces, rows in several pieces
+GRIDS = [(2, 2), (71, 142), (71, 143), (256, 128), (257, 128), (1100, 620), (2100, 1010)]
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    require_gpu()
+
+
+@pytest.mark.parametrize("nx,nr", GRIDS)
+def test_round_trip_and_fields(nx, nr):
+    """Populations read back are those set (they are exact in FP32), the
+    moments agree with the oracle's of the same populations to 2e-6 (FP32 sums
+    of nine populations), and a value that is not finite anywhere leaves the
+    state as it was."""
+    import oracle
+    from paper_1002_3028_amd import lbm
+    p = tiny_params(nx, nr, "closed", 1)
+    rng = np.random.default_rng(nx * nr)
+    w = np.array([4 / 9] + [1 / 9] * 4 + [1 / 36] * 4)[:, None, None]
+    f = (w * rng.uniform(0.95, 1.05, (9, nr, nx))).astype(np.float32).astype(np.float64)
+    g = rng.uniform(0.1, 0.2, (4, nr, nx)).astype(np.float32).astype(np.float64)
+    with lbm.Solver(p, "fp32") as s, oracle.RefSolver(p, threads=host_threads()) as r:
+        s.set_populations(f, g, 3)
+        r.set_populations(f, g, 3)
+        m, mr = s.moments(), r.moments()
+        for bad_f, bad_g in ((None, (3, nr - 1, nx - 1)), ((0, 0, 0), None)):
+            f2, g2 = f + 0.01, g.copy()
+            if bad_g:
+                g2[bad_g] = np.inf
+            if bad_f:
+                f2[bad_f] = np.nan
+            with pytest.raises(lbm.LbmError) as e:
+                s.set_populations(f2, g2, 8)
+            assert e.value.code == lbm.EINVAL and s.step_count == 3
+        f1, g1 = s.get_populations()
+    assert np.array_equal(f1, f) and np.array_equal(g1, g)
+    scale = np.abs(np.hypot(mr["ux"], mr["ur"])).max()
+    assert rel_err(m["rho"], mr["rho"]) < 2e-6 and rel_err(m["T"], mr["T"]) < 2e-6
+    assert np.abs(m["ux"] - mr["ux"]).max() < 2e-6 * max(scale, 1)
+    assert np.abs(m["ur"] - mr["ur"]).max() < 2e-6 * max(scale, 1)
+
+
+def test_batch_profiles_while_others_run():
+    """Profiles of running and finished jets, with and without work queued
+    since the last extraction, equal the moments' edges taken after a sync."""
+    from paper_1002_3028_amd import lbm
+    jets = [(tiny_params(300, 90, "jet", 1), 1 << 40), (tiny_params(64, 20, "jet", 0), 25)]
+    with lbm.Batch(1 << 28, 4, "fp32") as b, lbm.Batch(1 << 28, 4, "fp32") as c:
+        sb, sc = ([x.admit(p, None, n) for p, n in jets] for x in (b, c))
+        for k in (10, 10, 10, 7):
+            b.run(k)
+            c.run(k)
+            c.sync()
+            for q, w in zip(sb, sc):
+                for _ in range(2):
+                    pr, m = b.profiles(q), c.moments(w)
+                    assert np.array_equal(pr["ux_axis"], m["ux"][0])
+                    assert np.array_equal(pr["T_axis"], m["T"][0])
+                    assert np.array_equal(pr["ux_exit"], m["ux"][:, -1])
+                    assert np.array_equal(pr["T_exit"], m["T"][:, -1])
