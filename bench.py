@@ -64,7 +64,9 @@ def _ensure_built():
 
 
 def kernel_of(info):
-    return {1: "step_kernel", 2: "pair_kernel"}.get(info["steps"], "march_kernel")
+    if info["steps"] > 2:
+        return "stack_kernel" if info["by"] == 16 else "march_kernel"
+    return "pair_kernel" if info["steps"] == 2 else "step_kernel"
 
 
 def _summary(name):

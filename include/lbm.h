@@ -330,8 +330,9 @@ int lbm_tile_shape(int32_t index, int32_t *bx, int32_t *by, int32_t *ny, int32_t
  * bit-identical to two one-step launches, on every edge rule (with periodic
  * x edges the frame wraps to the other end of the domain).  Shapes with more
  * (S) run up to S steps per launch with waves that march up strips of
- * 64 - 2 (S - 1) columns, the intermediate states in registers (LDS holds
- * the property table), as bit-identical and on as many edge rules. */
+ * 64 - 2 (S - 1) columns (by = 4), or, on small grids, with 16 waves that
+ * hold a row each (by = 16), the intermediate states in registers, as
+ * bit-identical and on as many edge rules. */
 int lbm_tile_shape_info(int32_t index, int32_t *info, int32_t n);
 /* Select the launch variant of a handle (synchronises; EINVAL for an unknown
  * index, or any shape but 0 on a single-buffer handle, whose in-place kernel

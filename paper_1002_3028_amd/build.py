@@ -9,7 +9,7 @@ import tempfile
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblbm_hip.so")
-SOURCES = ["lbm_kernels.hip", "lbm_march.hip", "lbm_api.hip", "lbm_batch.hip"]
+SOURCES = ["lbm_kernels.hip", "lbm_march.hip", "lbm_stack.hip", "lbm_api.hip", "lbm_batch.hip"]
 ARCH = "gfx950"
 
 FLAGS = [

@@ -185,10 +185,10 @@ struct lbm_batch {
 
 namespace {
 
-// The requested (or default) shape for a cohort of `nodes` nodes.
-int pick_shape(const lbm_batch *b, int prec, int64_t nodes) {
+// The requested (or default) shape for a cohort.
+int pick_shape(const lbm_batch *b, int prec, const LaunchJets &jets) {
   if (b->layout == LBM_LAYOUT_SINGLE) return 0;  // the in-place kernel's tiles
-  return b->shape >= 0 ? b->shape : default_tile_shape(prec, nodes);
+  return b->shape >= 0 ? b->shape : default_tile_shape(prec, jets);
 }
 
 // Steps one launch of a tile shape advances.
@@ -278,18 +278,14 @@ int rebuild(lbm_batch *b) {
   int nsh;
   const TileShape *shapes = tile_shapes(&nsh);
   for (size_t c = 0; c < jets.size(); ++c) {
-    int64_t nodes = 0;
-    for (const JetDesc &d : jets[c]) nodes += (int64_t)d.nx * d.nr;
-    const int shape = meta[c].shape = pick_shape(b, meta[c].prec, nodes);
-    int32_t rows = 0;
-    if (marches(shapes[shape])) {
-      MarchJets sizes;
-      for (const JetDesc &d : jets[c]) sizes.emplace_back(d.nx, d.nr);
-      rows = march_rows(sizes, shape);
-    }
+    LaunchJets sizes;
+    for (const JetDesc &d : jets[c]) sizes.emplace_back(d.nx, d.nr);
+    const int shape = meta[c].shape = pick_shape(b, meta[c].prec, sizes);
+    const int32_t rows = marches(shapes[shape]) ? march_rows(sizes, shape) : 0;
     for (JetDesc &d : jets[c]) {
       b->slots[d.slot].shape = shape;
       d.tile_rows = rows;
+      d.tile_steps = shapes[shape].steps;
       start[c].push_back(start[c].back() + tiles_of(d.nx, d.nr, shape, rows, &d.tiles_x));
     }
   }

@@ -177,6 +177,7 @@ void fill_desc(JetDesc &d, const lbm_config *c) {
   d.g4_ref = (float)(0.25 * c->g_ref);
   d.flip = 0;
   d.tile_rows = 0;
+  d.tile_steps = 1;
 }
 
 int make_inlet(const lbm_config *c, int32_t n_t, const double *ux, const double *ur,
@@ -230,6 +231,8 @@ static const std::vector<TileShape> &shapes() {
     LBM_PAIR(16, 4, 5, 8),         LBM_PAIR(16, 4, 5, 12),
     // up to four steps per launch, waves marching up strips
     kMarch4,
+    // four to eight steps per launch, a wave per row
+    kStack[0], kStack[1], kStack[2], kStack[3],
   };
   return table;
 }
@@ -240,29 +243,51 @@ const TileShape *tile_shapes(int *count) {
   *count = (int)shapes().size();
   return shapes().data();
 }
-// FP32 storage: from 200 000 nodes in a launch four steps per launch (the
-// marching kernel): measured per step against the two-step kernel, 5.5
-// against 6.0 us on 1024 x 256, 7.5 / 8.9 on 1500 x 375, 9.9 / 13.1 on
-// 2048 x 512 and 32 / 57 on 4096 x 1024, but 5.0 / 4.6 on 1001 x 77 and 4.9
-// / 4.6 on 512 x 128, where a wave's halo rows outnumber its own.  Below, the
-// two-step kernel on 64 x 8 tiles with f_0 kept in registers (12-plane image,
-// 5 workgroups per CU).  16-bit storage: one step per launch.
-int default_tile_shape(int prec, int64_t nodes) {
-  if (prec != LBM_PREC_FP32) return 0;
-  int n;
+// The default shape, by the time a launch is expected to take per step (us,
+// measured; LaunchJets are the jets of one launch).
+//
+// Few nodes: stacked rows, as many steps per launch as leave one workgroup a
+// CU (a launch of one round takes 9.1, 10.0, 10.8 and 12.1 us for 4, 5, 6
+// and 8 steps in FP32, so 2.3 to 1.5 us per step, 16-bit forms 2.6 to 1.8
+// and, with stochastic rounding, 3.1 to 2.2; the one-step kernel takes 3.6
+// to 4.4 on the same grids).  A second round costs as much again: in FP32
+// that still pays (1024 x 256: 4.5 us per step, marching 5.5, one step 6.1),
+// in 16-bit storage it does not (768 x 192: FP16 4.4 against 4.45, with
+// stochastic rounding 5.1 against 4.7).
+// Many nodes: FP32 marches (against the two-step kernel 7.3 / 9.0 on 1500 x
+// 375, 9.9 / 13.1 on 2048 x 512, 32 / 57 on 4096 x 1024); 16-bit storage
+// takes one step per launch.
+int default_tile_shape(int prec, const LaunchJets &jets) {
+  const bool fp32 = prec == LBM_PREC_FP32;
+  const int cus = device_cus();
+  int n, best = 0;
   const TileShape *s = tile_shapes(&n);
-  for (int q = 0; q < n; ++q)
-    if (nodes >= 200000 ? marches(s[q])
-                        : s[q].steps == 2 && s[q].by == 4 && s[q].by * s[q].ny == 8 &&
-                              s[q].cache == 8)
-      return q;
-  return 0;
+  double best_t = 1e30;
+  for (int q = 0; q < n; ++q) {
+    const int k = s[q].steps;
+    double t;
+    if (s[q].stack_rows) {
+      int64_t wg = 0;
+      for (const auto &j : jets) wg += tiles_of(j.first, j.second, q, 0, nullptr);
+      const int64_t rounds = (wg + cus - 1) / cus;
+      if (!fp32 && rounds > 1) continue;
+      t = (2.3 + rounds * (k <= 6 ? 3.0 + k : 10.5)) / k;
+    } else if (marches(s[q]) && fp32) {
+      double us;
+      march_rows(jets, q, &us);
+      t = (5.5 + us) / k;
+    } else {
+      continue;
+    }
+    if (t < best_t) best = q, best_t = t;
+  }
+  return best;
 }
 
 int tiles_of(int32_t nx, int32_t nr, int shape, int32_t rows, int32_t *tiles_x) {
   const TileShape &s = shapes()[shape];
-  const int w = marches(s) ? s.bx - 2 * (s.steps - 1) : s.bx * s.nx;
-  const int h = s.by * (marches(s) ? rows : s.ny);
+  const int w = s.steps > 2 ? s.bx - 2 * (s.steps - 1) : s.bx * s.nx;
+  const int h = s.stack_rows ? s.stack_rows : s.by * (marches(s) ? rows : s.ny);
   const int tx = (nx + w - 1) / w;
   const int ty = (nr + h - 1) / h;
   if (tiles_x) *tiles_x = tx;
@@ -278,7 +303,7 @@ int tiles_of(int32_t nx, int32_t nr, int shape, int32_t rows, int32_t *tiles_x) 
 // to wait.  The height with the least work on the busiest CU wins: on
 // 2048 x 512 ten rows (468 workgroups, 9.9 us per step), not nine (540
 // workgroups, 12.4) or nineteen (252 workgroups, 11.4).
-int32_t march_rows(const MarchJets &jets, int shape) {
+int32_t march_rows(const LaunchJets &jets, int shape, double *us) {
   const TileShape &s = shapes()[shape];
   const int w = s.bx - 2 * (s.steps - 1), k = s.steps;
   const int cus = device_cus();
@@ -294,6 +319,7 @@ int32_t march_rows(const MarchJets &jets, int shape) {
     const double t = (double)(k * r + k * (k - 1)) * (0.67 * (per_cu / 2) + 0.44 * (per_cu % 2));
     if (r == 1 || t < best_t) best = r, best_t = t;
   }
+  if (us) *us = best_t;
   return best;
 }
 
@@ -310,7 +336,7 @@ int launch_step(int shape, int prec, bool big_table, int grid, hipStream_t st,
                 const JetDesc *jets, const int32_t *tiles, const BatchHdr *hdr, int32_t koff,
                 int32_t tog, int32_t nsteps, int32_t *flags) {
   const TileShape &s = shapes()[shape];
-  const void *fn = (big_table && marches(s) ? s.big : s.fn)[codec_index(prec)];
+  const void *fn = (big_table && s.big[0] ? s.big : s.fn)[codec_index(prec)];
   void *args[] = {(void *)&jets, (void *)&tiles, (void *)&hdr,   (void *)&koff,
                   (void *)&tog,  (void *)&nsteps, (void *)&flags};
   LBM_HIP(hipLaunchKernel(fn, dim3(grid), dim3(s.bx, s.by), args, 0, st));

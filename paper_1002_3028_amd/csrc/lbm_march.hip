@@ -11,7 +11,7 @@ namespace lbmx {
    (const void *)&march_kernel<CodecF16SR, K, NW, W, CP, LT>}
 #define LBM_MARCH(K, NW, W, CP)                                                  \
   {64, NW, 1, 1, W, CP, K, MARCH_TABLE * 16, LBM_MARCH_FN(K, NW, W, CP, true),   \
-   LBM_MARCH_FN(K, NW, W, CP, false)}
+   LBM_MARCH_FN(K, NW, W, CP, false), 0}
 
 const TileShape kMarch4 = LBM_MARCH(4, 4, 2, 0);
 

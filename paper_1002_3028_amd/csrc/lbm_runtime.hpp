@@ -59,13 +59,15 @@ int make_inlet(const lbm_config *c, int32_t n_t, const double *ux, const double 
 struct TileShape {
   int bx, by, ny, nx, waves, cache, steps, lds;
   const void *fn[4];  // FP32, FP16-dev, BF16-dev, FP16-dev rounded stochastically
-  const void *big[4]; // the marching kernel's instances for larger property tables
+  const void *big[4]; // instances for larger property tables (more than two steps)
+  int stack_rows;     // rows of a stacked tile (0: not the stacked-row kernel)
 };
 const TileShape *tile_shapes(int *count);
-extern const TileShape kMarch4;
-// The shape of a launch over `nodes` nodes of one storage form.
-int default_tile_shape(int prec, int64_t nodes);
-inline bool marches(const TileShape &s) { return s.big[0] != nullptr; }
+extern const TileShape kMarch4, kStack[4];
+typedef std::vector<std::pair<int32_t, int32_t>> LaunchJets;  // (nx, nr) each
+// The shape of a launch over jets of one storage form.
+int default_tile_shape(int prec, const LaunchJets &jets);
+inline bool marches(const TileShape &s) { return s.big[0] != nullptr && s.stack_rows == 0; }
 
 inline int codec_index(int prec) { return prec - LBM_PREC_FP32; }
 
@@ -106,9 +108,9 @@ int launch_encode(int prec, hipStream_t st, const JetDesc *d, const lbm_config *
 
 // Tiles of a jet, per row in *tiles_x; rows: the marching kernel's tile_rows.
 int tiles_of(int32_t nx, int32_t nr, int shape, int32_t rows, int32_t *tiles_x);
-// Rows of a wave's tile for jets (nx, nr) marched in one launch.
-typedef std::vector<std::pair<int32_t, int32_t>> MarchJets;
-int32_t march_rows(const MarchJets &jets, int shape);
+// Rows of a wave's tile for jets marched in one launch, and the time the
+// marching is expected to take.
+int32_t march_rows(const LaunchJets &jets, int shape, double *us = nullptr);
 int device_cus();  // of the current device
 bool big_table(const lbm_config *c);
 

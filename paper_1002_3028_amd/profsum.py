@@ -23,7 +23,7 @@ import os
 import statistics
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-KERNEL_SOURCES = ("lbm_device.hpp", "lbm_kernels.hpp", "lbm_march.hpp")
+KERNEL_SOURCES = ("lbm_device.hpp", "lbm_kernels.hpp", "lbm_march.hpp", "lbm_stack.hpp")
 
 
 def kernel_source_sha256() -> str:

@@ -1,5 +1,5 @@
 """Several time steps per launch with the intermediate states in registers
-(marching waves): bit-identical to one-step launches (shape 0) on every edge
+(marching waves, and stacked rows on small grids): bit-identical to one-step launches (shape 0) on every edge
 rule and storage form, at strips and tiles that end one node off an edge of
 the domain, on grids narrower than a strip or its halo, for step counts with
 a remainder, with property tables that fit LDS and tables that do not, and in
@@ -12,10 +12,12 @@ from gpu_common import CASES, noisy_inlet, require_gpu, tiny_params
 
 pytestmark = pytest.mark.gpu
 
-# (nx, nr): one strip (58 or 60 columns) and a column more or less; several
-# strips; narrower than the halo; the fewest rows; tiles that end on, before
-# and after the last row
-GRIDS = [(58, 16), (59, 17), (57, 2), (60, 64), (61, 65), (200, 45), (2, 3), (5, 9), (175, 130)]
+# (nx, nr): one strip (58 columns marching; 58, 56, 54 or 50 stacked) and a
+# column more or less; several strips; narrower than the halo; the fewest
+# rows; tiles (stacked: 10, 8, 6 or 2 rows) that end on, before and after the
+# last row
+GRIDS = [(58, 16), (59, 17), (57, 2), (50, 10), (56, 11), (55, 7), (200, 45), (2, 3), (5, 9),
+         (175, 130)]
 
 
 @pytest.fixture(scope="module", autouse=True)
