@@ -218,11 +218,12 @@ enum : int { STRIP_INNER = 0, STRIP_INLET = 1, STRIP_OUTFLOW = 2, STRIP_EDGE = 3
 
 // One wave's tile: strip i0 (of kind EK), rows j0 .. j1 - 1.  ready() is
 // called between the first row's loads and their use: the table in LDS is
-// complete after it.
+// complete after it.  late: the wave goes first for most of its rows (see
+// march_kernel).
 template <class C, int K, int CP, bool LT, int EK, class Ready>
 __device__ __forceinline__ bool march_tile(const JetDesc &jd, int64_t step, int32_t tog, int m,
-                                           int i0, int j0, int j1, const float4 *table,
-                                           const Ready &ready) {
+                                           int i0, int j0, int j1, bool late,
+                                           const float4 *table, const Ready &ready) {
   using T = typename C::T;
   using Word = typename Raw<sizeof(T)>::type;
   constexpr int ES = (int)sizeof(T);
@@ -407,6 +408,8 @@ __device__ __forceinline__ bool march_tile(const JetDesc &jd, int64_t step, int3
     if constexpr (N == K) fast_store(t - K + 1, q);
   };
   int t = tb;
+  const int calm = late ? tb + (te - tb) * 5 / 8 : te + 1;
+  if (late) __builtin_amdgcn_s_setprio(1);
   // away from the domain's first and last rows the levels start one by one,
   // two rows apart
   if (EK != STRIP_EDGE && m == K && tb >= 1 && tb + 2 * K - 3 <= nr - 2)
@@ -417,10 +420,13 @@ __device__ __forceinline__ bool march_tile(const JetDesc &jd, int64_t step, int3
   while (t <= te) {
     if ((t >= ts) & (t <= tf)) {
 #pragma unroll 1
-      do fast_row(Int<K>(), t++);
-      while (t <= tf);
+      do {
+        if (t == calm) __builtin_amdgcn_s_setprio(0);
+        fast_row(Int<K>(), t++);
+      } while (t <= tf);
       continue;
     }
+    if (t == calm) __builtin_amdgcn_s_setprio(0);
     const float4 q = qn;
     if (inlet) qn = in_load(t + 1);
     next_row(t);
@@ -451,6 +457,7 @@ __device__ __forceinline__ bool march_tile(const JetDesc &jd, int64_t step, int3
       store(j, q, m - 1, xcol | (j == 0) | (j == nr - 1));
     ++t;
   }
+  if (late) __builtin_amdgcn_s_setprio(0);
   return ok;
 }
 
@@ -476,6 +483,15 @@ __device__ __forceinline__ bool march_tile(const JetDesc &jd, int64_t step, int3
 // 2048 x 512, 43.6 on 4096 x 1024), with four 9.9 and 32.0 us (105 and 131
 // GLUPS); the two-step kernel takes 13.1 and 57.0.  W = 2 waves per SIMD: the
 // levels' rows need 190 VGPRs, and held to 128 the kernel spills.
+//
+// The workgroups fill the 256 CUs once before a second goes on each.  Of two
+// waves on a SIMD the older issues first, so that it would be done after
+// 22 us of a 2048 x 512 launch and leave the younger 10 us alone, in which
+// the SIMD can fill only two thirds of its issue slots.  The workgroups of
+// the second filling therefore go first for five eighths of their rows, and
+// both end together: 9.4 us per step against 10.1 (half of the rows 9.6, all
+// of them 10.2), 15.4 against 16.6 on 3000 x 700; 4096 x 1024, which waits
+// for memory more, keeps its 32.3.
 //
 // The edge rules act between levels as the step epilogue does on the ghost
 // ring (march_edges); the constant ghosts of equilibrium sides are read from
@@ -534,17 +550,18 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(W, 8)))
       table_of = jid;
       continue;
     }
+    const bool late = ((blockIdx.x >> 8) & 1) != 0;
     const bool px = d.bc[0] == BC_PERIODIC;
     const bool left_edge = !px & (i0 == 0), right_edge = !px & (d.nx <= i0 - HALO + 63);
     bool ok;
     if (!left_edge & !right_edge)
-      ok = march_tile<C, K, CP, LT, STRIP_INNER>(d, step, tog, m, i0, j0, j1, table, ready);
+      ok = march_tile<C, K, CP, LT, STRIP_INNER>(d, step, tog, m, i0, j0, j1, late, table, ready);
     else if (!right_edge & (d.bc[0] == BC_INLET))
-      ok = march_tile<C, K, CP, LT, STRIP_INLET>(d, step, tog, m, i0, j0, j1, table, ready);
+      ok = march_tile<C, K, CP, LT, STRIP_INLET>(d, step, tog, m, i0, j0, j1, late, table, ready);
     else if (!left_edge & (d.bc[1] == BC_OUTFLOW))
-      ok = march_tile<C, K, CP, LT, STRIP_OUTFLOW>(d, step, tog, m, i0, j0, j1, table, ready);
+      ok = march_tile<C, K, CP, LT, STRIP_OUTFLOW>(d, step, tog, m, i0, j0, j1, late, table, ready);
     else
-      ok = march_tile<C, K, CP, LT, STRIP_EDGE>(d, step, tog, m, i0, j0, j1, table, ready);
+      ok = march_tile<C, K, CP, LT, STRIP_EDGE>(d, step, tog, m, i0, j0, j1, late, table, ready);
     table_of = jid;
     if (!ok) flags[d.slot] = 1;
   }
