@@ -56,6 +56,9 @@ struct Slot {
 // would wait for the device, stalling a pipelined loop).
 constexpr size_t kBlockBytes = size_t(64) << 10;  // the table and 7 inlet rows of 512 nodes
 constexpr int32_t kPoolSlots = 512;
+// Pinned memory for results, at first: the profiles of a jet of up to 4096
+// columns and rows together.
+constexpr size_t kFirstResult = size_t(64) << 10;
 struct SlotBlock {
   void *p = nullptr;  // device
   void *h = nullptr;  // pinned host staging of the same size (the upload is
@@ -113,7 +116,8 @@ struct lbm_batch {
   Arena arena;
   std::vector<Slot> slots;
   std::vector<SlotBlock> blocks;   // per slot
-  void *pool_d = nullptr, *pool_h = nullptr;  // the first slots' blocks
+  char *d_mem = nullptr, *h_mem = nullptr;  // what the pointers below and the first
+                                            // slots' blocks point into
   std::vector<std::pair<void *, void *>> replaced;  // blocks freed with the batch
   // cohort lists, two copies (index `copy`): per cohort the compact list of
   // its jets, the tile prefix sums and the header
@@ -152,7 +156,8 @@ struct lbm_batch {
   // instability flags, one per slot, in pinned host memory (a step writes one
   // only when a jet has gone bad; the host reads it after the jet's results)
   int32_t *h_flags = nullptr, *d_flags = nullptr;
-  Pinned result;                   // profiles and small fields, written by kernels
+  char *first_result = nullptr;    // profiles and small fields, written by kernels:
+  Pinned result;                   // up to kFirstResult bytes, and larger ones
   // pinned staging of what rebuild uploads (cohort after cohort, compact), so
   // that the uploads are asynchronous copies ordered before the launches; two
   // copies, as the device lists
@@ -383,6 +388,12 @@ int io_after(lbm_batch *b, const Slot &sl) {
   return LBM_OK;
 }
 
+int result_mem(lbm_batch *b, size_t need, void **out) {
+  if (need > kFirstResult) return b->result.get(need, out);
+  *out = b->first_result;
+  return LBM_OK;
+}
+
 Slot *slot_of(lbm_batch *b, int32_t s) {
   if (!b || s < 0 || s >= (int32_t)b->slots.size() || !b->slots[s].used) return nullptr;
   return &b->slots[s];
@@ -409,30 +420,46 @@ int lbm_batch_create(size_t budget_bytes, int32_t max_slots, int32_t precision,
   b->max_cohorts = std::min<int32_t>(max_slots, 64);
   (void)hipGetDevice(&b->device);
   const size_t mc = (size_t)b->max_cohorts;
+  const size_t ms = (size_t)max_slots, pooled = std::min(ms, (size_t)kPoolSlots);
+  // one allocation of device memory and one of pinned memory hold everything
+  // small (an allocation takes 30 to 100 us), in parts aligned to 256 bytes
+  size_t nd = 0, nh = 0;
+  const auto part = [](size_t &end, size_t bytes) {
+    const size_t at = end;
+    end += align256(bytes);
+    return at;
+  };
+  const size_t d_pool = part(nd, pooled * kBlockBytes);
+  const size_t d_jets = part(nd, 2 * mc * ms * sizeof(JetDesc));
+  const size_t d_slot = part(nd, ms * sizeof(JetDesc));
+  const size_t d_tiles = part(nd, 2 * mc * (ms + 1) * sizeof(int32_t));
+  const size_t d_hdr = part(nd, 2 * mc * sizeof(BatchHdr));
+  const size_t h_pool = part(nh, pooled * kBlockBytes);
+  const size_t h_jets = part(nh, 2 * ms * sizeof(JetDesc));
+  const size_t h_slot = part(nh, ms * sizeof(JetDesc));
+  const size_t h_tiles = part(nh, 2 * (ms + mc) * sizeof(int32_t));
+  const size_t h_hdr = part(nh, 2 * mc * sizeof(BatchHdr));
+  const size_t h_flags = part(nh, ms * sizeof(int32_t));
+  const size_t h_first = part(nh, kFirstResult);
   bool ok = hipMalloc(&b->arena_mem, b->budget) == hipSuccess &&
-            hipMalloc(&b->d_jets, 2 * mc * max_slots * sizeof(JetDesc)) == hipSuccess &&
-            hipMalloc(&b->d_slot_desc, max_slots * sizeof(JetDesc)) == hipSuccess &&
-            hipMalloc(&b->d_tiles, 2 * mc * (max_slots + 1) * sizeof(int32_t)) == hipSuccess &&
-            hipMalloc(&b->d_hdr, 2 * mc * sizeof(BatchHdr)) == hipSuccess &&
-            hipHostMalloc((void **)&b->h_flags, max_slots * sizeof(int32_t),
-                          hipHostMallocDefault) == hipSuccess &&
-            hipHostGetDevicePointer((void **)&b->d_flags, b->h_flags, 0) == hipSuccess &&
-            hipHostMalloc(&b->h_jets, 2 * max_slots * sizeof(JetDesc), hipHostMallocDefault) ==
-                hipSuccess &&
-            hipHostMalloc(&b->h_tiles, 2 * (max_slots + mc) * sizeof(int32_t),
-                          hipHostMallocDefault) == hipSuccess &&
-            hipHostMalloc(&b->h_hdr, 2 * mc * sizeof(BatchHdr), hipHostMallocDefault) ==
-                hipSuccess &&
-            hipHostMalloc(&b->h_slot, max_slots * sizeof(JetDesc), hipHostMallocDefault) ==
-                hipSuccess;
-  void *first;  // (the profiles of jets of up to 4096 columns and rows)
-  ok = ok && b->result.get(size_t(64) << 10, &first) == LBM_OK;
-  const size_t pooled = (size_t)std::min(max_slots, kPoolSlots);
-  ok = ok && hipMalloc(&b->pool_d, pooled * kBlockBytes) == hipSuccess &&
-       hipHostMalloc(&b->pool_h, pooled * kBlockBytes, hipHostMallocDefault) == hipSuccess;
-  for (size_t q = 0; ok && q < pooled; ++q)
-    b->blocks[q] = SlotBlock{(char *)b->pool_d + q * kBlockBytes,
-                             (char *)b->pool_h + q * kBlockBytes, kBlockBytes, false};
+            hipMalloc((void **)&b->d_mem, nd) == hipSuccess &&
+            hipHostMalloc((void **)&b->h_mem, nh, hipHostMallocDefault) == hipSuccess &&
+            hipHostGetDevicePointer((void **)&b->d_flags, b->h_mem + h_flags, 0) == hipSuccess;
+  if (ok) {
+    b->d_jets = (JetDesc *)(b->d_mem + d_jets);
+    b->d_slot_desc = (JetDesc *)(b->d_mem + d_slot);
+    b->d_tiles = (int32_t *)(b->d_mem + d_tiles);
+    b->d_hdr = (BatchHdr *)(b->d_mem + d_hdr);
+    b->h_jets = (JetDesc *)(b->h_mem + h_jets);
+    b->h_slot = (JetDesc *)(b->h_mem + h_slot);
+    b->h_tiles = (int32_t *)(b->h_mem + h_tiles);
+    b->h_hdr = (BatchHdr *)(b->h_mem + h_hdr);
+    b->h_flags = (int32_t *)(b->h_mem + h_flags);
+    b->first_result = b->h_mem + h_first;
+    for (size_t q = 0; q < pooled; ++q)
+      b->blocks[q] = SlotBlock{b->d_mem + d_pool + q * kBlockBytes,
+                               b->h_mem + h_pool + q * kBlockBytes, kBlockBytes, false};
+  }
   // The runtime spreads a process's streams over a few hardware queues (four
   // by default), and work on streams that share a queue runs in submission
   // order.  The batch's own streams are created back to back -- the cohort
@@ -697,7 +724,7 @@ int lbm_batch_profiles(lbm_batch *b, int32_t slot, double *ux_axis, double *T_ax
   if (!sl) return LBM_EINVAL;
   const size_t nx = sl->cfg.nx, nr = sl->cfg.nr;
   void *v;
-  int rc = b->result.get(2 * (nx + nr) * sizeof(double), &v);
+  int rc = result_mem(b, 2 * (nx + nr) * sizeof(double), &v);
   if (rc) return rc;
   if ((rc = io_after(b, *sl))) return rc;
   if ((rc = launch_profiles(sl->prec, b->io, b->d_slot_desc + slot, &sl->cfg, sl->step,
@@ -726,7 +753,7 @@ int lbm_batch_moments(lbm_batch *b, int32_t slot, double *rho, double *ux, doubl
                                                              (4 * nx * (int64_t)sizeof(double))));
   void *v;
   const size_t need = 4 * nx * rows * sizeof(double);
-  int rc = small ? b->result.get(need, &v) : b->scratch.get(need, &v);
+  int rc = small ? result_mem(b, need, &v) : b->scratch.get(need, &v);
   if (rc) return rc;
   if ((rc = io_after(b, *sl))) return rc;
   for (int64_t j0 = 0; j0 < nr; j0 += rows) {
@@ -837,20 +864,11 @@ void lbm_batch_destroy(lbm_batch *b) {
     (void)hipFree(k.first);
     (void)hipHostFree(k.second);
   }
-  if (b->pool_d) (void)hipFree(b->pool_d);
-  if (b->pool_h) (void)hipHostFree(b->pool_h);
+  if (b->d_mem) (void)hipFree(b->d_mem);
+  if (b->h_mem) (void)hipHostFree(b->h_mem);
   b->scratch.release();
   if (b->arena_mem) (void)hipFree(b->arena_mem);
-  if (b->d_jets) (void)hipFree(b->d_jets);
-  if (b->d_slot_desc) (void)hipFree(b->d_slot_desc);
-  if (b->d_tiles) (void)hipFree(b->d_tiles);
-  if (b->d_hdr) (void)hipFree(b->d_hdr);
-  if (b->h_flags) (void)hipHostFree(b->h_flags);
   b->result.release();
-  if (b->h_jets) (void)hipHostFree(b->h_jets);
-  if (b->h_tiles) (void)hipHostFree(b->h_tiles);
-  if (b->h_hdr) (void)hipHostFree(b->h_hdr);
-  if (b->h_slot) (void)hipHostFree(b->h_slot);
   if (b->io) (void)hipStreamDestroy(b->io);
   if (b->cap) (void)hipStreamDestroy(b->cap);
   if (b->mark) (void)hipEventDestroy(b->mark);

@@ -255,14 +255,31 @@ const TileShape *tile_shapes(int *count) {
 // in 16-bit storage it does not (768 x 192: FP16 4.4 against 4.45, with
 // stochastic rounding 5.1 against 4.7).
 // Many nodes: FP32 marches (against the two-step kernel 7.3 / 9.0 on 1500 x
-// 375, 9.9 / 13.1 on 2048 x 512, 32 / 57 on 4096 x 1024); 16-bit storage
-// takes one step per launch.
+// 375, 9.4 / 13.1 on 2048 x 512, 32 / 57 on 4096 x 1024).  FP16 and BF16
+// move half the bytes and pay a rounding per level: a march takes 1.19 and
+// 1.25 times FP32's, and the line to the one-step kernel lies where its time,
+// fitted over the node count, is longer (FP16, one step / march: 8.2 / 8.4 on
+// 1536 x 384, 8.1 / 7.6 on 1024 x 512, 12.1 / 10.9 on 2048 x 512, 33 / 29.6
+// on 4096 x 1024, 97 / 62 on 6000 x 1500; BF16 8.3 / 8.9, 8.1 / 8.0, 12.2 /
+// 11.5, 33 / 31.7 and 98 / 66).  Cohorts of several jets run two at a time
+// and hide each other's launches, which is what a march saves in 16 bits: they
+// keep one step per launch (64 uneven jets: FP16 130 against 130 GLUPS, BF16
+// 128 against 121).
+// Stochastic rounding needs a key per level and takes one step per launch
+// (2048 x 512: 12.9 against 14.9).
 int default_tile_shape(int prec, const LaunchJets &jets) {
   const bool fp32 = prec == LBM_PREC_FP32;
   const int cus = device_cus();
   int n, best = 0;
   const TileShape *s = tile_shapes(&n);
   double best_t = 1e30;
+  int64_t nodes = 0;
+  for (const auto &j : jets) nodes += (int64_t)j.first * j.second;
+  // (what a march of 16-bit storage has to stay below, and its weight)
+  const double one_step = fp32 ? 1e30
+                          : prec == LBM_PREC_FP16SR || jets.size() > 1 ? 0.0
+                                                                       : 3.4 + 7.8e-6 * nodes;
+  const double weight = fp32 ? 1.0 : prec == LBM_PREC_FP16DEV ? 1.19 : 1.25;
   for (int q = 0; q < n; ++q) {
     const int k = s[q].steps;
     double t;
@@ -272,10 +289,11 @@ int default_tile_shape(int prec, const LaunchJets &jets) {
       const int64_t rounds = (wg + cus - 1) / cus;
       if (!fp32 && rounds > 1) continue;
       t = (2.3 + rounds * (k <= 6 ? 3.0 + k : 10.5)) / k;
-    } else if (marches(s[q]) && fp32) {
+    } else if (marches(s[q])) {
       double us;
       march_rows(jets, q, &us);
-      t = (5.5 + us) / k;
+      t = (5.5 + weight * us) / k;
+      if (t >= one_step) continue;
     } else {
       continue;
     }
@@ -298,10 +316,10 @@ int tiles_of(int32_t nx, int32_t nr, int shape, int32_t rows, int32_t *tiles_x) 
 // does K R + K (K - 1) collisions per column (its own and the halo rows that
 // its neighbours compute too), so tall tiles waste less, but the launch lasts
 // as long as the busiest CU: two workgroups of four waves share a CU (one
-// wave per SIMD leaves a third of the issue slots empty: 0.44 us per
-// collision of a wave alone, 0.33 us with two on the SIMD), and a third has
+// wave per SIMD leaves a third of the issue slots empty: 0.41 us per
+// collision of a wave alone, 0.31 us with two on the SIMD), and a third has
 // to wait.  The height with the least work on the busiest CU wins: on
-// 2048 x 512 ten rows (468 workgroups, 9.9 us per step), not nine (540
+// 2048 x 512 ten rows (468 workgroups, 9.4 us per step), not nine (540
 // workgroups, 12.4) or nineteen (252 workgroups, 11.4).
 int32_t march_rows(const LaunchJets &jets, int shape, double *us) {
   const TileShape &s = shapes()[shape];
@@ -316,7 +334,7 @@ int32_t march_rows(const LaunchJets &jets, int shape, double *us) {
     int64_t wg = 0;
     for (const auto &j : jets) wg += (int64_t)((j.first + w - 1) / w) * ((j.second + h - 1) / h);
     const int64_t per_cu = (wg + cus - 1) / cus;
-    const double t = (double)(k * r + k * (k - 1)) * (0.67 * (per_cu / 2) + 0.44 * (per_cu % 2));
+    const double t = (double)(k * r + k * (k - 1)) * (0.62 * (per_cu / 2) + 0.41 * (per_cu % 2));
     if (r == 1 || t < best_t) best = r, best_t = t;
   }
   if (us) *us = best_t;

@@ -212,9 +212,9 @@ __device__ __forceinline__ void below(const F &f) {
 }
 
 // Where a strip's ghost columns lie: none, column -1 with an inlet, column nx
-// with an outflow (the jet's two edges, whose rows cost little more than an
-// inner strip's), or any other rule or both.
-enum : int { STRIP_INNER = 0, STRIP_INLET = 1, STRIP_OUTFLOW = 2, STRIP_EDGE = 3 };
+// with an outflow or a wall (the edges of a free and of an impinging jet, whose
+// rows cost little more than an inner strip's), or any other rule or both.
+enum : int { STRIP_INNER = 0, STRIP_INLET, STRIP_OUTFLOW, STRIP_WALL, STRIP_EDGE };
 
 // One wave's tile: strip i0 (of kind EK), rows j0 .. j1 - 1.  ready() is
 // called between the first row's loads and their use: the table in LDS is
@@ -253,7 +253,7 @@ __device__ __forceinline__ bool march_tile(const JetDesc &jd, int64_t step, int3
   const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(dst_raw, 0, (int)span, BUF_WORD3);
   const MarchEdge<C> edge{{as_global(static_cast<const T *>(src_raw)), d.plane, d.pitch},
                           EK == STRIP_INLET || (EK == STRIP_EDGE && i0 == 0),
-                          EK == STRIP_OUTFLOW || (EK == STRIP_EDGE && nx <= i0 - HALO + 63),
+                          EK == STRIP_OUTFLOW || EK == STRIP_WALL || (EK == STRIP_EDGE && nx <= i0 - HALO + 63),
                           XE && i == -1, XE && i == nx, px ? il : i};
   const bool xcol = (i0 == 0) | (i0 + SW >= nx);  // owns a column that writes ring values
   // Inlet entries: lane l < K loads what the state after l + 1 steps takes at
@@ -294,6 +294,7 @@ __device__ __forceinline__ bool march_tile(const JetDesc &jd, int64_t step, int3
   bool ok = true;
   float f[9], g[4];
   uint32_t key = 0;
+  const float tw = EK == STRIP_WALL ? d.wallT[1] : 0.0f;  // (NaN: adiabatic)
   const auto next_row = [&](int t) {  // takes row t's loads, issues row t + 1's
 #pragma unroll
     for (int l = K - 1; l > 0; --l) rinv[l] = rinv[l - 1], rsq[l] = rsq[l - 1];
@@ -347,15 +348,21 @@ __device__ __forceinline__ bool march_tile(const JetDesc &jd, int64_t step, int3
       put(edge.at_right, from_left(f[7]), f[7]);
       put(edge.at_right, from_left(g[2]), g[2]);
       up[2] = f[6];
+    } else if constexpr (EK == STRIP_WALL) {
+      const float tg = tw == tw ? 0.5f * tw - from_left(ug[0]) : from_left(ug[0]);
+      put(edge.at_right, from_left(f[1]), f[3]);
+      put(edge.at_right, from_left(f[8]), lev[l].u1[2]);
+      put(edge.at_right, from_left(lev[l].u1[1]), f[7]);
+      put(edge.at_right, storage_round<C>(d, 11, tg, plane_key(key, 11)), g[2]);
     } else if constexpr (EK == STRIP_EDGE) {
       march_edges<C, true, false>(d, edge, j, f, g, ug, lev[l].u1, up, in_entry(q, l), key);
     }
   };
   const auto fast_store = [&](int j, const float4 &q) {
-    if constexpr (EK == STRIP_INLET || EK == STRIP_OUTFLOW) {
+    if constexpr (EK == STRIP_INLET || EK == STRIP_OUTFLOW || EK == STRIP_WALL) {
       const uint32_t at = vown + (uint32_t)(j + 1) * pitch_b;
-      const auto put = [&](int p, float v, uint32_t off) {
-        const T x = C::enc(v, pop_offset<C>(d, p), plane_key(key, p));
+      const auto put = [&](int p, float v, uint32_t off, int kp = -1) {
+        const T x = C::enc(v, pop_offset<C>(d, p), plane_key(key, kp < 0 ? p : kp));
         buf_store<ES, AUX_S>(__builtin_bit_cast(Word, x), rd, off, (uint32_t)p * plane_b);
       };
       const float4 e = in_entry(q, K - 1);
@@ -372,6 +379,12 @@ __device__ __forceinline__ bool march_tile(const JetDesc &jd, int64_t step, int3
           put(6, f[6], at + ES);
           put(7, f[7], at + ES);
           put(11, g[2], at + ES);
+        }
+        if (EK == STRIP_WALL && i == nx - 1) {  // (copies keep their key)
+          put(3, f[1], at + ES, 1);
+          put(6, f[8], at + ES - pitch_b, 8);
+          put(7, f[5], at + ES + pitch_b, 5);
+          put(11, tw == tw ? 0.5f * tw - g[0] : g[0], at + ES);
         }
       }
     } else {
@@ -480,7 +493,7 @@ __device__ __forceinline__ bool march_tile(const JetDesc &jd, int64_t step, int3
 // and addressing; beside it stand the launch (3.6 us), the first row's loads
 // (2 us) and the halo (1.3 of a 2048 x 512 jet's own collisions).  K = 4: with
 // three steps the launch and the memory weigh more (10.4 us per step on
-// 2048 x 512, 43.6 on 4096 x 1024), with four 9.9 and 32.0 us (105 and 131
+// 2048 x 512, 43.6 on 4096 x 1024), with four 9.4 and 32.0 us (111 and 131
 // GLUPS); the two-step kernel takes 13.1 and 57.0.  W = 2 waves per SIMD: the
 // levels' rows need 190 VGPRs, and held to 128 the kernel spills.
 //
@@ -560,6 +573,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(W, 8)))
       ok = march_tile<C, K, CP, LT, STRIP_INLET>(d, step, tog, m, i0, j0, j1, late, table, ready);
     else if (!left_edge & (d.bc[1] == BC_OUTFLOW))
       ok = march_tile<C, K, CP, LT, STRIP_OUTFLOW>(d, step, tog, m, i0, j0, j1, late, table, ready);
+    else if (!left_edge & (d.bc[1] == BC_WALL))
+      ok = march_tile<C, K, CP, LT, STRIP_WALL>(d, step, tog, m, i0, j0, j1, late, table, ready);
     else
       ok = march_tile<C, K, CP, LT, STRIP_EDGE>(d, step, tog, m, i0, j0, j1, late, table, ready);
     table_of = jid;
