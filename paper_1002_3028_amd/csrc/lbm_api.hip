@@ -92,7 +92,7 @@ int set_shape(lbm_handle *h, int shape) {
   if (shape < 0 || shape >= n) return LBM_EINVAL;
   if (h->layout == LBM_LAYOUT_SINGLE && shape != 0) return LBM_EINVAL;
   int32_t tx;
-  h->desc.tile_rows = marches(shapes[shape]) ? march_rows({{h->cfg.nx, h->cfg.nr}}, shape) : 0;
+  h->desc.tile_rows = marches(shapes[shape]) ? march_rows({launch_jet(h->cfg)}, shape) : 0;
   h->desc.tile_steps = shapes[shape].steps;
   h->ntiles = tiles_of(h->cfg.nx, h->cfg.nr, shape, h->desc.tile_rows, &tx);
   h->grid = (h->ntiles + 7) / 8 * 8;
@@ -231,7 +231,7 @@ int create_common(const lbm_config *cfg, void *dev_buf, size_t bytes, void *stre
   std::vector<float4> rows;
   make_inlet(&h->cfg, 0, nullptr, nullptr, nullptr, rows);
   if ((rc = upload_inlet(h, rows, 1)) ||
-      (rc = set_shape(h, h->layout == LBM_LAYOUT_SINGLE ? 0 : default_tile_shape(h->prec, {{cfg->nx, cfg->nr}})))) {
+      (rc = set_shape(h, h->layout == LBM_LAYOUT_SINGLE ? 0 : default_tile_shape(h->prec, {launch_jet(*cfg)})))) {
     release(h);
     return rc;
   }

@@ -284,7 +284,7 @@ int rebuild(lbm_batch *b) {
   const TileShape *shapes = tile_shapes(&nsh);
   for (size_t c = 0; c < jets.size(); ++c) {
     LaunchJets sizes;
-    for (const JetDesc &d : jets[c]) sizes.emplace_back(d.nx, d.nr);
+    for (const JetDesc &d : jets[c]) sizes.push_back(launch_jet(d));
     const int shape = meta[c].shape = pick_shape(b, meta[c].prec, sizes);
     const int32_t rows = marches(shapes[shape]) ? march_rows(sizes, shape) : 0;
     for (JetDesc &d : jets[c]) {

@@ -239,6 +239,8 @@ static const std::vector<TileShape> &shapes() {
 #undef LBM_SHAPE
 #undef LBM_PAIR
 
+constexpr int TWO_STEP = 23;  // the 64 x 8 tile with f_0 in registers: the fastest in FP32
+
 const TileShape *tile_shapes(int *count) {
   *count = (int)shapes().size();
   return shapes().data();
@@ -267,6 +269,11 @@ const TileShape *tile_shapes(int *count) {
 // 128 against 121).
 // Stochastic rounding needs a key per level and takes one step per launch
 // (2048 x 512: 12.9 against 14.9).
+// A march waits for its slowest wave, and the strips of an equilibrium side
+// or of a wall at column -1 read or write the ring row by row: such jets take
+// the two-step kernel in FP32 (2048 x 512 with four equilibrium sides: 13.7
+// against 17.0 us per step, 1024 x 512 between two walls: 8.6 against 8.8)
+// and one step in 16 bits (12.4 / 17.6, 7.7 / 10.1).
 int default_tile_shape(int prec, const LaunchJets &jets) {
   const bool fp32 = prec == LBM_PREC_FP32;
   const int cus = device_cus();
@@ -274,7 +281,8 @@ int default_tile_shape(int prec, const LaunchJets &jets) {
   const TileShape *s = tile_shapes(&n);
   double best_t = 1e30;
   int64_t nodes = 0;
-  for (const auto &j : jets) nodes += (int64_t)j.first * j.second;
+  bool plain = true;
+  for (const auto &j : jets) nodes += (int64_t)j.nx * j.nr, plain = plain && j.plain;
   // (what a march of 16-bit storage has to stay below, and its weight)
   const double one_step = fp32 ? 1e30
                           : prec == LBM_PREC_FP16SR || jets.size() > 1 ? 0.0
@@ -285,11 +293,13 @@ int default_tile_shape(int prec, const LaunchJets &jets) {
     double t;
     if (s[q].stack_rows) {
       int64_t wg = 0;
-      for (const auto &j : jets) wg += tiles_of(j.first, j.second, q, 0, nullptr);
+      for (const auto &j : jets) wg += tiles_of(j.nx, j.nr, q, 0, nullptr);
       const int64_t rounds = (wg + cus - 1) / cus;
       if (!fp32 && rounds > 1) continue;
       t = (2.3 + rounds * (k <= 6 ? 3.0 + k : 10.5)) / k;
-    } else if (marches(s[q])) {
+    } else if (fp32 && !plain && q == TWO_STEP) {
+      t = 4.3 + 8.9e-6 * nodes;
+    } else if (marches(s[q]) && plain) {
       double us;
       march_rows(jets, q, &us);
       t = (5.5 + weight * us) / k;
@@ -326,13 +336,13 @@ int32_t march_rows(const LaunchJets &jets, int shape, double *us) {
   const int w = s.bx - 2 * (s.steps - 1), k = s.steps;
   const int cus = device_cus();
   int32_t nr_max = 0;
-  for (const auto &j : jets) nr_max = std::max(nr_max, j.second);
+  for (const auto &j : jets) nr_max = std::max(nr_max, j.nr);
   int32_t best = 1;
   double best_t = 0.0;
   for (int32_t r = 1; r <= (nr_max + s.by - 1) / s.by; ++r) {
     const int32_t h = s.by * r;
     int64_t wg = 0;
-    for (const auto &j : jets) wg += (int64_t)((j.first + w - 1) / w) * ((j.second + h - 1) / h);
+    for (const auto &j : jets) wg += (int64_t)((j.nx + w - 1) / w) * ((j.nr + h - 1) / h);
     const int64_t per_cu = (wg + cus - 1) / cus;
     const double t = (double)(k * r + k * (k - 1)) * (0.62 * (per_cu / 2) + 0.41 * (per_cu % 2));
     if (r == 1 || t < best_t) best = r, best_t = t;

@@ -64,7 +64,19 @@ struct TileShape {
 };
 const TileShape *tile_shapes(int *count);
 extern const TileShape kMarch4, kStack[4];
-typedef std::vector<std::pair<int32_t, int32_t>> LaunchJets;  // (nx, nr) each
+// A jet of a launch.  plain: its edges are in line in the marching kernel (no
+// equilibrium side, no wall at column -1).
+struct LaunchJet {
+  int32_t nx, nr;
+  bool plain;
+};
+typedef std::vector<LaunchJet> LaunchJets;
+template <class D>  // lbm_config or JetDesc
+LaunchJet launch_jet(const D &d) {
+  bool plain = d.bc[0] != LBM_BC_WALL;
+  for (int s = 0; s < 4; ++s) plain = plain && d.bc[s] != LBM_BC_EQ;
+  return {d.nx, d.nr, plain};
+}
 // The shape of a launch over jets of one storage form.
 int default_tile_shape(int prec, const LaunchJets &jets);
 inline bool marches(const TileShape &s) { return s.big[0] != nullptr && s.stack_rows == 0; }

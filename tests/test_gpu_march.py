@@ -122,3 +122,16 @@ def test_march_flags_instability():
             s.set_inlet(*inputs.inlet_rows(16, 8.0, 0.9, 5.0))
             s.step(400)
             assert s.try_sync() == lbm.EUNSTABLE
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp16", "bf16", "fp16sr"])
+@pytest.mark.parametrize("case", CASES)
+def test_default_shape_equals_single(case, precision):
+    """The shape a solver takes by itself: on a grid where it is the stacked
+    rows, and on one of half a million nodes where storage form and edge rules
+    decide between marching, two steps and one step per launch."""
+    for nx, nr in [(600, 150), (1030, 515)]:
+        p = tiny_params(nx, nr, case, 0)
+        inlet = noisy_inlet(nr, 5, nx) if p["bc"][0] == "inlet" else None
+        ref = _state(p, inlet, 11, precision, tile_shape=0)
+        _same(_state(p, inlet, 11, precision), ref, (case, precision, nx, nr))
