@@ -233,6 +233,8 @@ static const std::vector<TileShape> &shapes() {
     kMarch4,
     // four to eight steps per launch, a wave per row
     kStack[0], kStack[1], kStack[2], kStack[3],
+    // up to five steps per launch, for states that the caches do not hold
+    kMarch5,
   };
   return table;
 }
@@ -260,15 +262,22 @@ const TileShape *tile_shapes(int *count) {
 // 375, 9.4 / 13.1 on 2048 x 512, 32 / 57 on 4096 x 1024).  FP16 and BF16
 // move half the bytes and pay a rounding per level: a march takes 1.19 and
 // 1.25 times FP32's, and the line to the one-step kernel lies where its time,
-// fitted over the node count, is longer (FP16, one step / march: 8.2 / 8.4 on
-// 1536 x 384, 8.1 / 7.6 on 1024 x 512, 12.1 / 10.9 on 2048 x 512, 33 / 29.6
-// on 4096 x 1024, 97 / 62 on 6000 x 1500; BF16 8.3 / 8.9, 8.1 / 8.0, 12.2 /
+// fitted over the node count, is longer, from half a million nodes (FP16, one
+// step / march: 7.4 / 8.2 on 1400 x 350, 8.2 / 8.4 on 1536 x 384, 8.1 / 7.6 on
+// 1024 x 512, 12.1 / 10.9 on 2048 x 512, 33 / 29.6 on 4096 x 1024, 97 / 62 on
+// 6000 x 1500; BF16 8.3 / 8.9, 8.1 / 8.0, 12.2 /
 // 11.5, 33 / 31.7 and 98 / 66).  Cohorts of several jets run two at a time
 // and hide each other's launches, which is what a march saves in 16 bits: they
 // keep one step per launch (64 uneven jets: FP16 130 against 130 GLUPS, BF16
 // 128 against 121).
-// Stochastic rounding needs a key per level and takes one step per launch
-// (2048 x 512: 12.9 against 14.9).
+// Stochastic rounding also needs a key per level (1.55 times FP32's march):
+// it marches only where one step per launch waits for HBM (2048 x 512 12.9 /
+// 14.0, 4096 x 1024 33.5 / 40.6, 6000 x 1500 97 / 84).
+// Both buffers of a jet in the 256 MiB of the Infinity Cache: four steps per
+// launch; beyond, FP32 takes five, since a launch then waits for HBM (four /
+// five steps: 15.1 / 15.8 us per step on 3000 x 700, 32.1 / 29.9 on 4096 x
+// 1024, 70 / 58 on 6000 x 1500; six 17.4, 34.3 and 64; FP16 62 / 63 on the
+// last).
 // A march waits for its slowest wave, and the strips of an equilibrium side
 // or of a wall at column -1 read or write the ring row by row: such jets take
 // the two-step kernel in FP32 (2048 x 512 with four equilibrium sides: 13.7
@@ -283,11 +292,17 @@ int default_tile_shape(int prec, const LaunchJets &jets) {
   int64_t nodes = 0;
   bool plain = true;
   for (const auto &j : jets) nodes += (int64_t)j.nx * j.nr, plain = plain && j.plain;
+  const bool cached = 2 * NPOP * (fp32 ? 4 : 2) * nodes <= int64_t(256) << 20;
   // (what a march of 16-bit storage has to stay below, and its weight)
-  const double one_step = fp32 ? 1e30
-                          : prec == LBM_PREC_FP16SR || jets.size() > 1 ? 0.0
-                                                                       : 3.4 + 7.8e-6 * nodes;
-  const double weight = fp32 ? 1.0 : prec == LBM_PREC_FP16DEV ? 1.19 : 1.25;
+  const double one_step =
+      fp32 ? 1e30
+      : jets.size() > 1 || nodes < 500000 ? 0.0
+      : cached ? std::min(3.4 + 7.8e-6 * nodes, 5.0 + 6.6e-6 * nodes)
+               : 10.7e-6 * nodes;
+  const double weight = fp32                       ? 1.0
+                        : prec == LBM_PREC_FP16DEV ? 1.19
+                        : prec == LBM_PREC_BF16DEV ? 1.25
+                                                   : 1.55;
   for (int q = 0; q < n; ++q) {
     const int k = s[q].steps;
     double t;
@@ -299,7 +314,7 @@ int default_tile_shape(int prec, const LaunchJets &jets) {
       t = (2.3 + rounds * (k <= 6 ? 3.0 + k : 10.5)) / k;
     } else if (fp32 && !plain && q == TWO_STEP) {
       t = 4.3 + 8.9e-6 * nodes;
-    } else if (marches(s[q]) && plain) {
+    } else if (marches(s[q]) && plain && k == (fp32 && !cached ? 5 : 4)) {
       double us;
       march_rows(jets, q, &us);
       t = (5.5 + weight * us) / k;

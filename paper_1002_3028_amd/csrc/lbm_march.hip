@@ -14,6 +14,7 @@ namespace lbmx {
    LBM_MARCH_FN(K, NW, W, CP, false), 0}
 
 const TileShape kMarch4 = LBM_MARCH(4, 4, 2, 0);
+const TileShape kMarch5 = LBM_MARCH(5, 4, 2, 0);
 
 bool big_table(const lbm_config *c) { return c->table_n > MARCH_TABLE; }
 

@@ -494,7 +494,8 @@ __device__ __forceinline__ bool march_tile(const JetDesc &jd, int64_t step, int3
 // (2 us) and the halo (1.3 of a 2048 x 512 jet's own collisions).  K = 4: with
 // three steps the launch and the memory weigh more (10.4 us per step on
 // 2048 x 512, 43.6 on 4096 x 1024), with four 9.4 and 32.0 us (111 and 131
-// GLUPS); the two-step kernel takes 13.1 and 57.0.  W = 2 waves per SIMD: the
+// GLUPS); the two-step kernel takes 13.1 and 57.0.  K = 5 pays where the
+// state is larger than the caches: 29.9 us on 4096 x 1024.  W = 2 waves per SIMD: the
 // levels' rows need 190 VGPRs, and held to 128 the kernel spills.
 //
 // The workgroups fill the 256 CUs once before a second goes on each.  Of two

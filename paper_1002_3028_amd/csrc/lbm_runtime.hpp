@@ -63,7 +63,7 @@ struct TileShape {
   int stack_rows;     // rows of a stacked tile (0: not the stacked-row kernel)
 };
 const TileShape *tile_shapes(int *count);
-extern const TileShape kMarch4, kStack[4];
+extern const TileShape kMarch4, kMarch5, kStack[4];
 // A jet of a launch.  plain: its edges are in line in the marching kernel (no
 // equilibrium side, no wall at column -1).
 struct LaunchJet {
