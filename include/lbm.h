@@ -237,9 +237,10 @@ int lbm_probe_copy(void *dst, const void *src, size_t bytes, void *hip_stream);
  * carved out of budget_bytes of device memory.  lbm_batch_run advances every
  * active jet by up to k steps: the active jets are grouped into cohorts of
  * at most cohort_bytes of buffers (default 128 MiB, so that the two cohorts
- * in flight at once fill the 256 MiB Infinity Cache), and each cohort gets k
- * steps of one persistent launch per step over all its jets (HIP graphs),
- * cohorts alternating between two streams (lbm_batch_set_streams).  A jet
+ * in flight at once fill the 256 MiB Infinity Cache; jets that the streams'
+ * cohorts hold together are shared out evenly), and each cohort gets k steps
+ * of persistent launches, of one to eight steps each, over all its jets (HIP
+ * graphs), cohorts alternating between two streams (lbm_batch_set_streams).  A jet
  * stops at its own target step count.  Each jet's result is bitwise the
  * same as that of the same jet run alone.  `precision` is the batch's
  * storage form; a jet admitted with another (cfg->precision) joins cohorts

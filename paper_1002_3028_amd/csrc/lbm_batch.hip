@@ -59,6 +59,9 @@ constexpr int32_t kPoolSlots = 512;
 // Pinned memory for results, at first: the profiles of a jet of up to 4096
 // columns and rows together.
 constexpr size_t kFirstResult = size_t(64) << 10;
+
+// Population buffers from which jets of one cohort are split over the streams.
+constexpr size_t kSplitBytes = size_t(32) << 20;
 struct SlotBlock {
   void *p = nullptr;  // device
   void *h = nullptr;  // pinned host staging of the same size (the upload is
@@ -230,6 +233,43 @@ Lists lists_of(const lbm_batch *b, int32_t cp) {
           b->d_hdr + cp * mc, b->h_hdr + cp * mc};
 }
 
+// The active jets (one storage form, in *order) shared out to one cohort per
+// stream, the largest first, each to the lightest cohort: the cohort of each,
+// *order then sorted by it.  Empty if they are filled up one after another
+// instead: several forms, more than the streams' cohorts may hold together, or
+// so little that a launch's work is smaller than its fixed part.  Cohorts on
+// two streams overlap each other's launches and tails, which a set that fits
+// one cohort, or one and a bit, would not (FP16SR, admission to last profile:
+// 8 jets of 79 MiB 4.2 -> 3.2 ms, 4 jets of 48 MiB 3.6 -> 3.0; 6 of 23 MiB
+// 2.65 and 2.70).
+std::vector<int32_t> split_evenly(const lbm_batch *b, std::vector<int32_t> *order) {
+  const size_t n = order->size(), k = std::min<size_t>(b->nstreams, b->max_cohorts);
+  size_t total = 0;
+  for (int32_t s : *order) {
+    if (b->slots[s].prec != b->slots[order->front()].prec) return {};
+    total += b->slots[s].bytes;
+  }
+  if (n < 2 || k < 2 || !b->cohort_bytes || total < kSplitBytes || total > k * b->cohort_bytes)
+    return {};
+  std::vector<int32_t> large = *order;
+  std::stable_sort(large.begin(), large.end(), [&](int32_t x, int32_t y) {
+    return b->slots[x].bytes > b->slots[y].bytes;
+  });
+  std::vector<size_t> load(k, 0);
+  std::vector<int32_t> part_of(b->slots.size(), 0);
+  for (int32_t s : large) {
+    const size_t c = std::min_element(load.begin(), load.end()) - load.begin();
+    part_of[s] = (int32_t)c;
+    load[c] += b->slots[s].bytes;
+  }
+  if (*std::max_element(load.begin(), load.end()) > b->cohort_bytes) return {};
+  std::stable_sort(order->begin(), order->end(),
+                   [&](int32_t x, int32_t y) { return part_of[x] < part_of[y]; });
+  std::vector<int32_t> part;
+  for (int32_t s : *order) part.push_back(part_of[s]);
+  return part;
+}
+
 // Rebuild and upload the cohorts: active jets by storage form (the batch's
 // first), in slot order within a form; a new cohort at every change of form
 // and whenever the next jet's buffers would take the cohort past
@@ -247,6 +287,7 @@ int rebuild(lbm_batch *b) {
   };
   std::stable_sort(order.begin(), order.end(),
                    [&](int32_t x, int32_t y) { return form_key(x) < form_key(y); });
+  const std::vector<int32_t> part = split_evenly(b, &order);
   // storage forms after each position's own (cohorts kept for them: a form
   // change always opens a cohort; max_cohorts >= the forms present, since it
   // is at least min(max_slots, 64))
@@ -262,9 +303,11 @@ int rebuild(lbm_batch *b) {
     const int32_t s = order[q];
     Slot &sl = b->slots[s];
     const bool other_form = !jets.back().empty() && meta.back().prec != sl.prec;
-    const bool full = b->cohort_bytes && !jets.back().empty() &&
-                      bytes.back() + sl.bytes > b->cohort_bytes &&
-                      (int32_t)jets.size() + later[q] < b->max_cohorts;
+    const bool full =
+        !part.empty() ? q > 0 && part[q] != part[q - 1]
+                      : b->cohort_bytes && !jets.back().empty() &&
+                            bytes.back() + sl.bytes > b->cohort_bytes &&
+                            (int32_t)jets.size() + later[q] < b->max_cohorts;
     if (other_form || full) {
       jets.emplace_back();
       start.emplace_back(1, 0);

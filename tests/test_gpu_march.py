@@ -135,3 +135,30 @@ def test_default_shape_equals_single(case, precision):
         inlet = noisy_inlet(nr, 5, nx) if p["bc"][0] == "inlet" else None
         ref = _state(p, inlet, 11, precision, tile_shape=0)
         _same(_state(p, inlet, 11, precision), ref, (case, precision, nx, nr))
+
+
+@pytest.mark.parametrize("streams", [1, 2, 3, 4])
+def test_batch_split_over_streams(streams):
+    """Jets whose buffers (52 MB) are split evenly over the streams' cohorts,
+    one far larger than the rest, retired one after another until the rest is
+    too little to split: each equals itself alone."""
+    from paper_1002_3028_amd import lbm
+    sizes = [(300, 70, 31), (1500, 200, 40), (700, 150, 52), (290, 60, 64)]
+    jets = [(tiny_params(nx, nr, "jet", q % 2), noisy_inlet(nr, 3, q), n)
+            for q, (nx, nr, n) in enumerate(sizes)]
+    refs = []
+    for p, inlet, n in jets:
+        with lbm.Batch(1 << 28, 1, "fp32") as alone:
+            alone.set_launch(0, 0)
+            s = alone.admit(p, inlet, n)
+            alone.run(n)
+            refs.append(alone.moments(s))
+    with lbm.Batch(1 << 28, 8, "fp32") as b:
+        b.set_streams(streams)
+        slots = [b.admit(*j) for j in jets]
+        for _ in range(13):
+            b.run(5)
+        for s, r in zip(slots, refs):
+            m = b.moments(s)
+            for k in r:
+                assert np.array_equal(m[k], r[k]), (streams, s, k)
