@@ -17,7 +17,7 @@ storage (13 populations read and written) and 52 B for 16-bit storage.
 the launch duration, from HIP events on the solver's stream around the step
 launches of the timed region (`event_us_per_launch`).  The average duration
 of the same kernel in the committed rocprofv3 summary is given beside it
-(`rocprof_us_per_launch`).  A two-step launch updates each node twice while
+(`rocprof_us_per_launch`).  A launch of m steps updates each node m times while
 reading and writing each population once; `traffic` is the HBM bytes one
 launch moves by the rocprofv3 counters (committed summary), and
 `traffic_GBps` their rate.

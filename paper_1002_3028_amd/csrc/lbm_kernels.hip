@@ -272,7 +272,7 @@ const TileShape *tile_shapes(int *count) {
 // 128 against 121).
 // Stochastic rounding also needs a key per level (1.55 times FP32's march):
 // it marches only where one step per launch waits for HBM (2048 x 512 12.9 /
-// 14.0, 4096 x 1024 33.5 / 40.6, 6000 x 1500 97 / 84).
+// 14.3, 4096 x 1024 33.5 / 40.6, 6000 x 1500 97 / 84).
 // Both buffers of a jet in the 256 MiB of the Infinity Cache: four steps per
 // launch; beyond, FP32 takes five, since a launch then waits for HBM (four /
 // five steps: 15.1 / 15.8 us per step on 3000 x 700, 32.1 / 29.9 on 4096 x
