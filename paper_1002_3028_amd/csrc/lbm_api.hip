@@ -487,11 +487,12 @@ int lbm_set_graph_steps(lbm_handle *h, int32_t k) {
 int lbm_set_tile_shape(lbm_handle *h, int32_t index) {
   if (!h) return LBM_EINVAL;
   LBM_HIP(hipStreamSynchronize(h->stream));
-  // bring the descriptor's step0 up to date before re-uploading it
-  h->base = h->step;
+  // (a refused index leaves the handle as it is: the device's descriptor may
+  // lag behind the step count, and base and dflip say by how much)
   const int rc = set_shape(h, index);
+  if (rc) return rc;
   drop_graph(h);
-  return rc ? rc : prepare_graph(h);
+  return prepare_graph(h);
 }
 
 int lbm_moments(lbm_handle *h, double *rho, double *ux, double *ur, double *T) {
