@@ -72,3 +72,19 @@ def test_16bit_full_size_first_200_steps(reference, precision, bound):
     errs = field_errors(_run(p, inlet, precision), mr)
     print(json.dumps({"grid": "4096x1024", "steps": STEPS, "precision": precision, **errs}))
     assert errs["profile"] < bound
+
+
+def test_default_shape_full_size_first_200_steps(reference):
+    """The shape a solver takes by itself at this size (in FP32 five steps per
+    launch, marching): FP32 within the same bound of the oracle and, in FP32 and
+    FP16, the bits of one step per launch."""
+    p, inlet, mr = reference
+    for precision in ("fp32", "fp16"):
+        m = _run(p, inlet, precision)
+        one = _run(p, inlet, precision, tile_shape=0)
+        for key in m:
+            assert np.array_equal(one[key], m[key]), (precision, key)
+        if precision == "fp32":
+            eu, eT = rel_err(speed(m), speed(mr)), rel_err(m["T"], mr["T"])
+            print(f"4096x1024, default shape, {STEPS} steps: |u| {eu:.2e}  T {eT:.2e}")
+            assert eu < 1e-4 and eT < 1e-4

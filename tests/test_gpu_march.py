@@ -162,3 +162,24 @@ def test_batch_split_over_streams(streams):
             m = b.moments(s)
             for k in r:
                 assert np.array_equal(m[k], r[k]), (streams, s, k)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp16", "bf16", "fp16sr"])
+@pytest.mark.parametrize("case", CASES)
+def test_tall_tiles_and_second_filling(case, precision):
+    """1030 x 515: both marching shapes take five rows a wave, so that most of
+    a wave's rows have all levels active, and more workgroups (468 with four
+    steps per launch, 494 with five) than the device has CUs, so that the
+    waves of the second filling run too.  Launches of every step count up to
+    the shape's."""
+    from paper_1002_3028_amd import lbm
+    nx, nr = 1030, 515
+    p = tiny_params(nx, nr, case, 1)
+    inlet = noisy_inlet(nr, 5, nx) if p["bc"][0] == "inlet" else None
+    ref = _state(p, inlet, 13, precision, tile_shape=0)
+    marching = [q for q in _march_shapes() if lbm.tile_shape_info(q)["by"] == 4]
+    assert sorted(lbm.tile_shape_info(q)["steps"] for q in marching) == [4, 5]
+    for q in marching:
+        _same(_state(p, inlet, 13, precision, tile_shape=q), ref, (case, precision, q))
+        _same(_state(p, inlet, 13, precision, tile_shape=q, graph_steps=11), ref,
+              (case, precision, q, "graph"))

@@ -88,3 +88,23 @@ def test_fp16_largest_grid(case):
     e = _errors(_run(p, inlet, st, "fp16"), ref)
     print(json.dumps({"grid": f"{NX}x{NR}", "precision": "fp16", **e}))
     assert e["u"] < 5e-3 and e["T"] < 5e-3 and e["profiles"] < 5e-3
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp16", "fp16sr"])
+def test_default_shape_largest_grid_full_launches(case, precision):
+    """Thirteen steps in the shape a solver takes by itself (marching): launches
+    with all their levels, which three steps do not reach, and one of the rest;
+    bit-identical to one step per launch."""
+    from paper_1002_3028_amd import lbm
+    p, inlet, st, _ = case
+    got = []
+    for kw in ({}, {"tile_shape": 0}):
+        print(f"max grid {NX}x{NR}: {precision} {kw}", flush=True)
+        with lbm.Solver(p, precision, **kw) as s:
+            s.set_state(*st)
+            s.set_inlet(*inlet)
+            s.step(13)
+            got.append((s.moments(), s.conservation()))
+    for key in got[0][0]:
+        assert np.array_equal(got[0][0][key], got[1][0][key]), key
+    assert got[0][1] == got[1][1]
