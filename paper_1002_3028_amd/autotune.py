@@ -1,19 +1,21 @@
 """Launch autotuner of the step kernels.
 
-Single jets (best_shape): for a precision and a size class it times every
-compiled tile shape (block shape, nodes per lane, cache policy, one or two
-steps per launch) on a representative jet and keeps the fastest.  Size
-classes follow the memory system: the two population buffers either fit the
-256 MB Infinity Cache with room to spare, or do not.
+Single jets (best_shape): for a precision, a grid and the kind of its edges
+and table it times every compiled tile shape (block shape, nodes per lane,
+cache policy, one to eight steps per launch) on the jet and keeps the fastest.
+Size classes follow the memory system: the two population buffers either fit
+the 256 MB Infinity Cache with room to spare, or do not.
 
 Batches (tune_batch): for a set of jets advanced together it searches the
 tile shape, the persistent grid, the cohort size and the number of streams.
 
-Results are cached as JSON keyed by GPU architecture, precision and size
-class in $LBM_AUTOTUNE_CACHE or ~/.cache/lbmx/autotune.json.
+Results are cached as JSON in $LBM_AUTOTUNE_CACHE or
+~/.cache/lbmx/autotune.json, keyed by what the fastest shape depends on: GPU
+architecture, the set of compiled shapes, precision, grid, edges and table.
 """
 from __future__ import annotations
 
+import hashlib
 import json
 import os
 import time
@@ -89,18 +91,47 @@ def time_shapes(params: dict, inlet, precision: str, steps: int = 200, warmup: i
     return out
 
 
+def _shapes_tag() -> str:
+    """Digest of the compiled shapes: results are reused only while the set
+    that they were chosen from is the same."""
+    return hashlib.sha256(json.dumps(lbm.tile_shape_infos(), sort_keys=True)
+                          .encode()).hexdigest()[:8]
+
+
+def _edges(params: dict) -> str:
+    """The edge rules as the kernels tell them apart: an equilibrium side or a
+    wall at column -1 costs shapes of several steps per launch a quarter or
+    more, and the others little."""
+    bc = params.get("bc", ())
+    eq = lbm.BC["eq"]
+    special = any(v in ("eq", eq) for v in bc) or tuple(bc)[:1] in (("wall",), (lbm.BC["wall"],))
+    return "special" if special else "plain"
+
+
+def _table(params: dict) -> str:
+    """Whether the property table is larger than the 256 entries that shapes
+    of more than two steps per launch hold in LDS."""
+    t = params.get("nu_mult")
+    return "large" if t is not None and len(t) > 256 else "lds"
+
+
+def shape_key(params: dict, precision: str, steps: int | None = None) -> str:
+    """Cache key of best_shape.  The grid itself is part of it: shapes of
+    several steps per launch go by rounds of workgroups, and the fastest on
+    one grid can take several times the default's time on another of the same
+    class (eight stacked steps on 128 x 32 and on 400 x 300)."""
+    key = (f"{_arch()}/{_shapes_tag()}/{params['nx']}x{params['nr']}/{_edges(params)}/"
+           f"{_table(params)}/{precision}/{size_class(lbm.bytes_required(params, precision))}")
+    if "periodic" in tuple(params.get("bc", ()))[:2]:
+        key += "/periodic"
+    return key if steps is None else f"{key}/steps{steps}"
+
+
 def best_shape(params: dict, inlet, precision: str, retune: bool = False,
                steps: int | None = None) -> int:
-    """Fastest tile shape for this jet's size class (tuned once, cached);
-    steps = 1 or 2 restricts the choice to shapes taking that many steps per
-    launch."""
-    ws = lbm.bytes_required(params, precision)
-    key = f"{_arch()}/{precision}/{size_class(ws)}"
-    periodic = "periodic" in tuple(params.get("bc", ()))[:2]
-    if periodic:
-        key += "/periodic"
-    if steps is not None:
-        key += f"/steps{steps}"
+    """Fastest tile shape for this jet (tuned once per shape_key, cached);
+    steps restricts the choice to shapes taking that many steps per launch."""
+    key = shape_key(params, precision, steps)
     db = _load()
     infos = lbm.tile_shape_infos()
     hit = db.get(key)
@@ -124,10 +155,13 @@ BATCH_STREAMS = (1, 2, 3)
 def batch_key(jets, precision: str) -> str:
     """Cache key of a set of jets: precision, jet count and total population
     bytes (to the nearest power of two) -- the two things the best cohort
-    split and grid depend on."""
+    split and grid depend on -- and, for the shape, the compiled set and
+    whether any jet has special edges or a large table."""
     import math
     total = sum(lbm.bytes_required(p, precision) for p, _ in jets)
-    return (f"{_arch()}/{precision}/batch/{len(jets)}jets/"
+    edges = "special" if any(_edges(p) == "special" for p, _ in jets) else "plain"
+    table = "large" if any(_table(p) == "large" for p, _ in jets) else "lds"
+    return (f"{_arch()}/{_shapes_tag()}/{edges}/{table}/{precision}/batch/{len(jets)}jets/"
             f"{2 ** round(math.log2(max(total, 1 << 20)) - 20)}MiB")
 
 
