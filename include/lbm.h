@@ -202,7 +202,10 @@ int lbm_set_graph_steps(lbm_handle *h, int32_t k);
 int lbm_set_state(lbm_handle *h, const double *rho, const double *ux,
                   const double *ur, const double *T);
 /* Stored post-collision populations, decoded to double: f 9*nr*nx, g 4*nr*nx
- * (population index slowest). */
+ * (population index slowest).  Device memory on top of the handle's own, kept
+ * until it is destroyed: reading populations or fields at most 64 MiB,
+ * setting populations 52 bytes a node and at most 64 MiB (down to 1 MiB where
+ * the device has no more). */
 int lbm_get_populations(lbm_handle *h, double *f, double *g);
 int lbm_set_populations(lbm_handle *h, const double *f, const double *g,
                         int64_t step);

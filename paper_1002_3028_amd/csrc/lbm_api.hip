@@ -410,6 +410,12 @@ int red_blocks(const lbm_handle *h) {
   return (int)std::min<int64_t>(kMaxRedBlocks, (nodes + RED_THREADS - 1) / RED_THREADS);
 }
 
+// Of the values e0 .. e0 + n - 1 of all populations: how many are f's (the
+// first nine planes; g's follow).
+int64_t f_part(int64_t e0, int64_t n, int64_t nodes) {
+  return std::max<int64_t>(0, std::min(9 * nodes, e0 + n) - e0);
+}
+
 // Both conservation entry points: reduce into `part` (nblocks partials), the
 // total into the host block, and wait.
 int conservation_into(lbm_handle *h, RedPartial *part, int nblocks, double *mass3d,
@@ -497,15 +503,15 @@ int lbm_set_tile_shape(lbm_handle *h, int32_t index) {
 
 int lbm_moments(lbm_handle *h, double *rho, double *ux, double *ur, double *T) {
   if (!h) return LBM_EINVAL;
-  const int64_t nx = h->cfg.nx, nodes = nx * h->cfg.nr;
+  const int64_t nodes = (int64_t)h->cfg.nx * h->cfg.nr;
   double *const to[4] = {rho, ux, ur, T};
   const int32_t view = view_of(h, h->step);
   int rc;
   void *p;
   if (4 * nodes * sizeof(double) <= PINNED_RESULT) {
     if ((rc = h->result.get(4 * nodes * sizeof(double), &p))) return rc;
-    if ((rc = launch_moments(h->prec, h->stream, h->d_desc, &h->cfg, h->step, view, 0, h->cfg.nr,
-                             (double *)p, nodes, h->d_flag)))
+    if ((rc = launch_moments(h->prec, h->stream, h->d_desc, h->step, view, 0, nodes, (double *)p,
+                             h->d_flag)))
       return rc;
     const int st = sync_and_check(h);
     if (st == LBM_EDEVICE) return st;
@@ -513,18 +519,17 @@ int lbm_moments(lbm_handle *h, double *rho, double *ux, double *ur, double *T) {
       if (to[q]) std::memcpy(to[q], (double *)p + q * nodes, nodes * sizeof(double));
     return st;
   }
-  const int32_t rows = (int32_t)std::min<int64_t>(
-      h->cfg.nr, std::max<int64_t>(1, (int64_t)PIECE_BYTES / (4 * nx * (int64_t)sizeof(double))));
-  if ((rc = h->piece.get(4 * nx * rows * sizeof(double), &p))) return rc;
-  for (int32_t j0 = 0; j0 < h->cfg.nr; j0 += rows) {
-    const int32_t n = std::min(rows, h->cfg.nr - j0);
-    if ((rc = launch_moments(h->prec, h->stream, h->d_desc, &h->cfg, h->step, view, j0, n,
-                             (double *)p, nx * n, h->d_flag)))
+  int64_t most;
+  if ((rc = h->piece.piece(nodes, 4 * sizeof(double), &p, &most))) return rc;
+  for (int64_t n0 = 0; n0 < nodes; n0 += most) {
+    const int64_t n = std::min(most, nodes - n0);
+    if ((rc = launch_moments(h->prec, h->stream, h->d_desc, h->step, view, n0, n, (double *)p,
+                             h->d_flag)))
       return rc;
     LBM_HIP(hipStreamSynchronize(h->stream));
     for (int q = 0; q < 4; ++q)
       if (to[q])
-        LBM_HIP(hipMemcpy(to[q] + nx * j0, (double *)p + q * nx * n, nx * n * sizeof(double),
+        LBM_HIP(hipMemcpy(to[q] + n0, (double *)p + q * n, n * sizeof(double),
                           hipMemcpyDeviceToHost));
   }
   return sync_and_check(h);
@@ -599,7 +604,7 @@ int lbm_get_populations(lbm_handle *h, double *f, double *g) {
   void *p;
   if (NPOP * one <= PINNED_RESULT) {
     if ((rc = h->result.get(NPOP * one, &p))) return rc;
-    if ((rc = launch_decode(h->prec, h->stream, h->d_desc, &h->cfg, h->step, view, 0, NPOP,
+    if ((rc = launch_decode(h->prec, h->stream, h->d_desc, h->step, view, 0, NPOP * nodes,
                             (double *)p)))
       return rc;
     const int st = sync_and_check(h);
@@ -608,20 +613,18 @@ int lbm_get_populations(lbm_handle *h, double *f, double *g) {
     if (g) std::memcpy(g, (double *)p + 9 * nodes, 4 * one);
     return st;
   }
-  const int planes = (int)std::min<size_t>(NPOP, std::max<size_t>(1, PIECE_BYTES / one));
-  if ((rc = h->piece.get(planes * one, &p))) return rc;
-  for (int q0 = 0; q0 < NPOP; q0 += planes) {
-    const int n = std::min(planes, NPOP - q0);
-    if ((rc = launch_decode(h->prec, h->stream, h->d_desc, &h->cfg, h->step, view, q0, n,
-                            (double *)p)))
+  int64_t most;
+  if ((rc = h->piece.piece(NPOP * nodes, sizeof(double), &p, &most))) return rc;
+  for (int64_t e0 = 0; e0 < NPOP * nodes; e0 += most) {
+    const int64_t n = std::min(most, NPOP * nodes - e0);
+    if ((rc = launch_decode(h->prec, h->stream, h->d_desc, h->step, view, e0, n, (double *)p)))
       return rc;
     LBM_HIP(hipStreamSynchronize(h->stream));
-    // (planes of one array follow each other in it: one copy)
-    const int nf = std::max(0, std::min(9, q0 + n) - q0);
+    const int64_t nf = f_part(e0, n, nodes);
     if (nf > 0 && f)
-      LBM_HIP(hipMemcpy(f + q0 * nodes, p, nf * one, hipMemcpyDeviceToHost));
+      LBM_HIP(hipMemcpy(f + e0, p, nf * sizeof(double), hipMemcpyDeviceToHost));
     if (n > nf && g)
-      LBM_HIP(hipMemcpy(g + (q0 + nf - 9) * nodes, (double *)p + nf * nodes, (n - nf) * one,
+      LBM_HIP(hipMemcpy(g + (e0 + nf - 9 * nodes), (double *)p + nf, (n - nf) * sizeof(double),
                         hipMemcpyDeviceToHost));
   }
   return sync_and_check(h);
@@ -646,17 +649,16 @@ int lbm_set_populations(lbm_handle *h, const double *f, const double *g, int64_t
                             &h->host->bad_input)))
       return rc;
   } else {
-    const int planes = (int)std::min<size_t>(NPOP, std::max<size_t>(1, PIECE_BYTES / one));
-    if ((rc = h->piece.get(planes * one, &p))) return rc;
-    for (int q0 = 0; q0 < NPOP; q0 += planes) {
-      const int n = std::min(planes, NPOP - q0);
-      const int nf = std::max(0, std::min(9, q0 + n) - q0);
+    int64_t most;
+    if ((rc = h->piece.piece(NPOP * nodes, sizeof(double), &p, &most))) return rc;
+    for (int64_t e0 = 0; e0 < NPOP * nodes; e0 += most) {
+      const int64_t n = std::min(most, NPOP * nodes - e0), nf = f_part(e0, n, nodes);
       LBM_HIP(hipStreamSynchronize(h->stream));  // (the last piece has been read)
-      if (nf > 0) LBM_HIP(hipMemcpy(p, f + q0 * nodes, nf * one, hipMemcpyHostToDevice));
+      if (nf > 0) LBM_HIP(hipMemcpy(p, f + e0, nf * sizeof(double), hipMemcpyHostToDevice));
       if (n > nf)
-        LBM_HIP(hipMemcpy((double *)p + nf * nodes, g + (q0 + nf - 9) * nodes, (n - nf) * one,
+        LBM_HIP(hipMemcpy((double *)p + nf, g + (e0 + nf - 9 * nodes), (n - nf) * sizeof(double),
                           hipMemcpyHostToDevice));
-      if ((rc = launch_narrow(h->stream, (const double *)p, (float *)v + q0 * nodes, n * nodes,
+      if ((rc = launch_narrow(h->stream, (const double *)p, (float *)v + e0, n,
                               &h->host->bad_input)))
         return rc;
     }

@@ -786,30 +786,27 @@ int lbm_batch_moments(lbm_batch *b, int32_t slot, double *rho, double *ux, doubl
                       double *T) {
   Slot *sl = slot_of(b, slot);
   if (!sl) return LBM_EINVAL;
-  const int64_t nx = sl->cfg.nx, nr = sl->cfg.nr, nodes = nx * nr;
+  const int64_t nodes = (int64_t)sl->cfg.nx * sl->cfg.nr;
   double *const to[4] = {rho, ux, ur, T};
   const int32_t view = state_view_of(b->layout, sl->step, sl->flip);
   const bool small = 4 * nodes * sizeof(double) <= PINNED_RESULT;
-  const int64_t rows =
-      small ? nr
-            : std::min<int64_t>(nr, std::max<int64_t>(1, (int64_t)PIECE_BYTES /
-                                                             (4 * nx * (int64_t)sizeof(double))));
+  int64_t most = nodes;
   void *v;
-  const size_t need = 4 * nx * rows * sizeof(double);
-  int rc = small ? result_mem(b, need, &v) : b->scratch.get(need, &v);
+  int rc = small ? result_mem(b, 4 * nodes * sizeof(double), &v)
+                 : b->scratch.piece(nodes, 4 * sizeof(double), &v, &most);
   if (rc) return rc;
   if ((rc = io_after(b, *sl))) return rc;
-  for (int64_t j0 = 0; j0 < nr; j0 += rows) {
-    const int64_t n = std::min(rows, nr - j0);
-    if ((rc = launch_moments(sl->prec, b->io, b->d_slot_desc + slot, &sl->cfg, sl->step, view,
-                             (int32_t)j0, (int32_t)n, (double *)v, nx * n, nullptr)))
+  for (int64_t n0 = 0; n0 < nodes; n0 += most) {
+    const int64_t n = std::min(most, nodes - n0);
+    if ((rc = launch_moments(sl->prec, b->io, b->d_slot_desc + slot, sl->step, view, n0, n,
+                             (double *)v, nullptr)))
       return rc;
     if ((rc = extracted(b))) return rc;
     for (int q = 0; q < 4; ++q) {
-      const double *p = (const double *)v + q * nx * n;
+      const double *p = (const double *)v + q * n;
       if (!to[q]) continue;
-      if (small) std::memcpy(to[q] + nx * j0, p, nx * n * sizeof(double));
-      else LBM_HIP(hipMemcpy(to[q] + nx * j0, p, nx * n * sizeof(double), hipMemcpyDeviceToHost));
+      if (small) std::memcpy(to[q] + n0, p, n * sizeof(double));
+      else LBM_HIP(hipMemcpy(to[q] + n0, p, n * sizeof(double), hipMemcpyDeviceToHost));
     }
   }
   return b->h_flags[slot] ? LBM_EUNSTABLE : LBM_OK;

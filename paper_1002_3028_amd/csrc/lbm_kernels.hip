@@ -462,12 +462,12 @@ int launch_ghost_fill(int prec, hipStream_t st, const JetDesc *d, const lbm_conf
   return LBM_OK;
 }
 
-int launch_moments(int prec, hipStream_t st, const JetDesc *d, const lbm_config *c,
-                   int64_t step, int32_t view, int32_t j0, int32_t rows, double *out,
-                   int64_t stride, int32_t *flags) {
+int launch_moments(int prec, hipStream_t st, const JetDesc *d,
+                   int64_t step, int32_t view, int64_t n0, int64_t n, double *out,
+                   int32_t *flags) {
   const auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3((c->nx + 255) / 256, rows), dim3(256), 0, st, d, step, view,
-                       j0, out, stride, flags);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, d, step, view,
+                       (int32_t)n0, (int32_t)n, out, flags);
   };
   if (prec == LBM_PREC_FP32) go(moments_kernel<CodecF32>);
   else if (prec == LBM_PREC_FP16DEV) go(moments_kernel<CodecF16>);
@@ -513,11 +513,11 @@ int launch_conservation(int prec, hipStream_t st, const JetDesc *d, int64_t node
   return LBM_OK;
 }
 
-int launch_decode(int prec, hipStream_t st, const JetDesc *d, const lbm_config *c, int64_t step,
-                  int32_t view, int32_t p0, int32_t planes, double *out) {
+int launch_decode(int prec, hipStream_t st, const JetDesc *d, int64_t step, int32_t view,
+                  int64_t e0, int64_t n, double *out) {
   const auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3((c->nx + 255) / 256, c->nr, planes), dim3(256), 0, st, d, step,
-                       view, p0, out);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, d, step, view,
+                       (int32_t)e0, (int32_t)n, out);
   };
   if (prec == LBM_PREC_FP32) go(decode_kernel<CodecF32>);
   else if (prec == LBM_PREC_FP16DEV) go(decode_kernel<CodecF16>);

@@ -612,17 +612,18 @@ __global__ void init_kernel(const JetDesc *__restrict__ dp, int64_t step, int32_
     st.put(d, p, i, j, eq_plane(p, q.x, q.y, q.z, q.w), plane_key(key, p));
 }
 
-// Pre-collision moments (eq. 2) of the state after `step` steps, rows j0 to
-// j0 + gridDim.y - 1: four arrays of doubles (rho, ux, ur, T), i fastest,
-// `stride` apart, as the caller's arrays hold them.  flags (if given): set
-// where rho or T is not finite or rho <= 0.
+// Pre-collision moments (eq. 2) of the state after `step` steps, nodes n0 to
+// n0 + n - 1 in the order of the caller's arrays (i fastest): four arrays of n
+// doubles (rho, ux, ur, T).  flags (if given): set where rho or T is not
+// finite or rho <= 0.
 template <class C>
 __global__ void moments_kernel(const JetDesc *__restrict__ dp, int64_t step, int32_t view,
-                               int32_t j0, double *__restrict__ out, int64_t stride,
+                               int32_t n0, int32_t n, double *__restrict__ out,
                                int32_t *__restrict__ flags) {
   const JetDesc &d = *dp;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x, j = j0 + (int)blockIdx.y;
-  if (i >= d.nx) return;
+  const int32_t q = blockIdx.x * blockDim.x + threadIdx.x;
+  if (q >= n) return;
+  const int j = (n0 + q) / d.nx, i = n0 + q - j * d.nx;
   const State<C> s = state_view<C>(d, view);
   float f[9], g[4];
   pulled_node<C>(d, s, i, j, f, g);
@@ -630,11 +631,11 @@ __global__ void moments_kernel(const JetDesc *__restrict__ dp, int64_t step, int
   const float mx = (f[1] + f[5] + f[8]) - (f[3] + f[6] + f[7]);
   const float mr = (f[2] + f[5] + f[6]) - (f[4] + f[7] + f[8]);
   const float T = (g[0] + g[1]) + (g[2] + g[3]);
-  double *o = out + (int64_t)blockIdx.y * d.nx + i;
+  double *o = out + q;
   o[0] = rho;
-  o[stride] = mx / rho;
-  o[2 * stride] = mr / rho;
-  o[3 * stride] = T;
+  o[n] = mx / rho;
+  o[2 * (int64_t)n] = mr / rho;
+  o[3 * (int64_t)n] = T;
   if (flags && !((rho > 0.0f) && (rho < __builtin_inff()) && (fabsf(T) < __builtin_inff())))
     flags[d.slot] = 1;
 }
@@ -700,19 +701,20 @@ __global__ __launch_bounds__(RED_THREADS) void conservation_kernel(
   if (threadIdx.x == 0) partial[blockIdx.x] = RedPartial{sm[0], se[0], sb[0], 0.0};
 }
 
-// Stored populations p0 .. -> dense planes of doubles (nr x nx, no pitch).
+// Stored populations -> doubles, values e0 to e0 + n - 1 of the dense planes
+// (13 x nr x nx, no pitch).
 template <class C>
 __global__ void decode_kernel(const JetDesc *__restrict__ dp, int64_t step, int32_t view,
-                              int32_t p0, double *__restrict__ out) {
+                              int32_t e0, int32_t n, double *__restrict__ out) {
   const JetDesc &d = *dp;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x, j = blockIdx.y;
-  const int p = p0 + (int)blockIdx.z;
-  if (i >= d.nx) return;
-  out[((int64_t)blockIdx.z * d.nr + j) * d.nx + i] = state_view<C>(d, view).load(d, p, i, j);
+  const int32_t q = blockIdx.x * blockDim.x + threadIdx.x;
+  if (q >= n) return;
+  const int32_t nodes = d.nx * d.nr, p = (e0 + q) / nodes, node = e0 + q - p * nodes;
+  const int j = node / d.nx, i = node - j * d.nx;
+  out[q] = state_view<C>(d, view).load(d, p, i, j);
 }
 
 // Dense FP32 planes (13 x nr x nx, no pitch) -> stored populations.
-
 template <class C>
 __global__ void encode_kernel(const JetDesc *__restrict__ dp, int64_t step, int32_t view,
                               const float *__restrict__ in) {

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -105,15 +106,14 @@ int launch_init(int prec, hipStream_t st, const JetDesc *d, const lbm_config *c,
                 int32_t view, const float4 *state, float4 u0);
 int launch_ghost_fill(int prec, hipStream_t st, const JetDesc *d, const lbm_config *c,
                       int64_t step, int32_t view);
-int launch_moments(int prec, hipStream_t st, const JetDesc *d, const lbm_config *c,
-                   int64_t step, int32_t view, int32_t j0, int32_t rows, double *out,
-                   int64_t stride, int32_t *flags);
+int launch_moments(int prec, hipStream_t st, const JetDesc *d, int64_t step, int32_t view,
+                   int64_t n0, int64_t n, double *out, int32_t *flags);
 int launch_profiles(int prec, hipStream_t st, const JetDesc *d, const lbm_config *c,
                     int64_t step, int32_t view, double *out);
 int launch_conservation(int prec, hipStream_t st, const JetDesc *d, int64_t nodes, int64_t step,
                         int32_t view, RedPartial *partial, int nblocks, RedPartial *out);
-int launch_decode(int prec, hipStream_t st, const JetDesc *d, const lbm_config *c, int64_t step,
-                  int32_t view, int32_t p0, int32_t planes, double *out);
+int launch_decode(int prec, hipStream_t st, const JetDesc *d, int64_t step, int32_t view,
+                  int64_t e0, int64_t n, double *out);
 int launch_narrow(hipStream_t st, const double *in, float *out, int64_t n, int32_t *bad);
 int launch_encode(int prec, hipStream_t st, const JetDesc *d, const lbm_config *c, int64_t step,
                   int32_t view, const float *in);
@@ -134,8 +134,8 @@ int resident_workgroups(int shape, int prec, bool single_buffer);
 // bytes the kernel writes them straight into pinned host memory: one launch
 // and one wait (profiles of a 128 x 32 jet 20 us with the binding; device
 // memory, two copies back and a conversion on the host took 48).  Larger ones
-// go through device memory in pieces of PIECE_BYTES and are copied to the
-// caller's arrays at the copy engine's rate, with no pass over them on the
+// go through device memory in pieces of at most PIECE_BYTES (any run of nodes
+// or values, so that no grid needs more) and are copied to the caller's arrays at the copy engine's rate, with no pass over them on the
 // host (populations out and in and fields of a 1024 x 256 jet: 3.6 ms, with
 // host conversions 7.4).
 constexpr size_t PINNED_RESULT = size_t(1) << 20;
@@ -150,6 +150,7 @@ struct Pinned {
       release();
       if (hipHostMalloc(&p, need, hipHostMallocDefault) != hipSuccess) {
         p = nullptr;
+        (void)hipGetLastError();
         return LBM_ENOMEM;
       }
       bytes = need;
@@ -173,11 +174,24 @@ struct Scratch {
       if (p) (void)hipFree(p);
       p = nullptr;
       bytes = 0;
-      if (hipMalloc(&p, need) != hipSuccess) return LBM_ENOMEM;
+      if (hipMalloc(&p, need) != hipSuccess) {
+        p = nullptr;
+        (void)hipGetLastError();  // (the caller's code says it; no later call shall)
+        return LBM_ENOMEM;
+      }
       bytes = need;
     }
     *out = p;
     return LBM_OK;
+  }
+  // Room for a piece of `total` items of `item` bytes: all of them, at most
+  // PIECE_BYTES, and down to 1 MiB where the device has no more to give.
+  int piece(int64_t total, size_t item, void **out, int64_t *n) {
+    size_t room = std::min((size_t)total * item, PIECE_BYTES);
+    int rc;
+    while ((rc = get(room, out)) == LBM_ENOMEM && room > PINNED_RESULT) room /= 2;
+    *n = (int64_t)(room / item);
+    return rc;
   }
   void release() {
     if (p) (void)hipFree(p);

@@ -71,3 +71,56 @@ def test_batch_profiles_while_others_run():
                     assert np.array_equal(pr["T_axis"], m["T"][0])
                     assert np.array_equal(pr["ux_exit"], m["ux"][:, -1])
                     assert np.array_equal(pr["T_exit"], m["T"][:, -1])
+
+
+@pytest.mark.parametrize("nx,nr", [(3000000, 2), (4200, 4100)])
+def test_pieces_stay_small(nx, nr):
+    """A row of fields (96 MB) or a plane of populations (138 MB) larger than a
+    piece: reading fields and populations back takes at most 64 MiB of device
+    memory (allocations are in steps of 2 MiB), restoring them 52 bytes a node
+    more, and the values are those of the profiles and the ones set."""
+    import torch
+    from paper_1002_3028_amd import lbm
+    p = tiny_params(nx, nr, "closed", 1)
+    rng = np.random.default_rng(nx)
+    line = rng.uniform(0.95, 1.05, nx + 12).astype(np.float32).astype(np.float64)
+
+    def values(k):
+        return np.stack([(0.1 + 0.01 * q) * np.broadcast_to(line[q:q + nx], (nr, nx)) *
+                         (1.0 + np.arange(nr) % 3)[:, None] for q in range(k)]
+                        ).astype(np.float32).astype(np.float64)
+    f, g = values(9), values(4)
+    piece, slack = 64 << 20, 4 << 20
+
+    def used():
+        torch.cuda.synchronize()
+        free, total = torch.cuda.mem_get_info()
+        return total - free
+
+    with lbm.Solver(p, "fp32") as s:
+        s.sync()
+        u0 = used()
+        m = s.moments()
+        s.get_populations()
+        u1 = used()
+        s.set_populations(f, g, 3)
+        u2 = used()
+        print(f"{nx}x{nr}: reading {u1 - u0}, restoring {u2 - u1}", flush=True)
+        assert u1 - u0 <= piece + slack
+        assert u2 - u0 <= 52 * nx * nr + piece + slack
+        f1, g1 = s.get_populations()
+        assert np.array_equal(f1, f) and np.array_equal(g1, g)
+        m, pr = s.moments(), s.profiles()
+        assert np.array_equal(pr["ux_axis"], m["ux"][0])
+        assert np.array_equal(pr["T_axis"], m["T"][0])
+        assert np.array_equal(pr["ux_exit"], m["ux"][:, -1])
+        assert np.array_equal(pr["T_exit"], m["T"][:, -1])
+    with lbm.Batch(lbm.bytes_required(p) + (1 << 20), 1, "fp32") as b:
+        slot = b.admit(p, None, 10)
+        b.run(4)
+        u0 = used()
+        m = b.moments(slot)
+        assert used() - u0 <= piece + slack
+        pr = b.profiles(slot)
+        assert np.array_equal(pr["ux_axis"], m["ux"][0])
+        assert np.array_equal(pr["T_exit"], m["T"][:, -1])
