@@ -806,8 +806,12 @@ int lbm_batch_moments(lbm_batch *b, int32_t slot, double *rho, double *ux, doubl
       const double *p = (const double *)v + q * n;
       if (!to[q]) continue;
       if (small) std::memcpy(to[q] + n0, p, n * sizeof(double));
-      else LBM_HIP(hipMemcpy(to[q] + n0, p, n * sizeof(double), hipMemcpyDeviceToHost));
+      else
+        LBM_HIP(hipMemcpyAsync(to[q] + n0, p, n * sizeof(double), hipMemcpyDeviceToHost, b->io));
     }
+    // (a plain hipMemcpy would wait for all that the process has put on the
+    // default stream)
+    if (!small) LBM_HIP(hipStreamSynchronize(b->io));
   }
   return b->h_flags[slot] ? LBM_EUNSTABLE : LBM_OK;
 }

@@ -124,3 +124,27 @@ def test_pieces_stay_small(nx, nr):
         pr = b.profiles(slot)
         assert np.array_equal(pr["ux_axis"], m["ux"][0])
         assert np.array_equal(pr["T_exit"], m["T"][:, -1])
+
+
+def test_batch_fields_do_not_wait_for_other_streams():
+    """Large fields of a batch's jet come back while work that the program put
+    on the default stream (about 150 ms) is still running."""
+    import torch
+    from paper_1002_3028_amd import lbm
+    p = tiny_params(1100, 620, "jet", 1)
+    a = torch.ones(8192, 8192, device="cuda", dtype=torch.bfloat16)
+    with lbm.Batch(1 << 28, 1, "fp32") as b:
+        slot = b.admit(p, None, 10)
+        b.run(10)
+        b.sync()
+        ref = b.moments(slot)
+        other = torch.cuda.Event()
+        for _ in range(200):
+            a @ a
+        other.record()
+        m = b.moments(slot)
+        waited = other.query()
+        torch.cuda.synchronize()
+    assert not waited
+    for k in ref:
+        assert np.array_equal(m[k], ref[k]), k
