@@ -878,6 +878,7 @@ int lbm_batch_set_streams(lbm_batch *b, int32_t n) {
   LBM_HIP(hipStreamSynchronize(b->stream));
   for (hipStream_t s : b->side)
     if (s) LBM_HIP(hipStreamSynchronize(s));
+  b->dirty = true;  // (how the jets are shared out depends on the streams)
   bool ok = b->fork || hipEventCreateWithFlags(&b->fork, hipEventDisableTiming) == hipSuccess;
   for (int32_t q = 0; ok && q + 1 < n; ++q) {
     if (!b->side[q] && hipStreamCreateWithFlags(&b->side[q], hipStreamNonBlocking) != hipSuccess)

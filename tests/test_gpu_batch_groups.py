@@ -1,0 +1,68 @@
+"""How a batch's jets are shared out over cohorts, seen by the kernel launches
+of a group (torch's profiler): it follows the number of streams, also when that
+changes between runs, and never changes a result."""
+import collections
+import warnings
+
+import numpy as np
+import pytest
+
+from gpu_common import noisy_inlet, require_gpu, tiny_params
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    require_gpu()
+
+
+def _launches(b, k):
+    """Graph launches and step kernels of one run of k steps."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    b.run(k)  # (captures)
+    b.sync()
+    with warnings.catch_warnings():
+        warnings.simplefilter("ignore")
+        with profile(activities=[ProfilerActivity.CUDA]) as prof:
+            b.run(k)
+            b.sync()
+        torch.cuda.synchronize()
+        seen = collections.Counter(e.name for e in prof.events())
+    graphs = sum(n for name, n in seen.items() if "GraphLaunch" in name)
+    steps = sum(n for name, n in seen.items() if "lbmx::" in name and "advance" not in name)
+    if not steps:
+        pytest.skip("no kernel trace on this machine")
+    return graphs, steps
+
+
+def _uneven():
+    sizes = [(512, 128), (300, 70), (1500, 200), (700, 150), (512, 140), (640, 160)]
+    return [(tiny_params(nx, nr, "jet", q % 2), noisy_inlet(nr, 3, q)) for q, (nx, nr)
+            in enumerate(sizes)]
+
+
+def test_cohorts_follow_the_number_of_streams():
+    """Six FP16 jets (40 MB of buffers) share two streams evenly and run as one
+    cohort on one stream, whichever came first; the fields are those of the
+    jets run alone."""
+    from paper_1002_3028_amd import lbm
+    jets = _uneven()
+    taken = 0
+    with lbm.Batch(1 << 28, 8, "fp16") as b:
+        slots = [b.admit(p, inlet, 1 << 40) for p, inlet in jets]
+        for n in (1, 2, 1, 3, 2):
+            b.set_streams(n)
+            graphs, steps = _launches(b, 20)
+            taken += 40
+            assert graphs == n, (n, graphs, steps)
+        got = [b.moments(s) for s in slots]
+    for (p, inlet), m in zip(jets, got):
+        with lbm.Solver(p, "fp16", tile_shape=0) as s:
+            if inlet is not None:
+                s.set_inlet(*inlet)
+            s.step(taken)
+            ref = s.moments()
+        for key in ref:
+            assert np.array_equal(m[key], ref[key]), (p["nx"], key)
