@@ -62,8 +62,7 @@ struct lbm_handle {
   // whose arguments are fixed, first brings them up to date)
   int64_t base = 0;
   int32_t dflip = 0;
-  int shape = 0;
-  int32_t ntiles = 0, grid = 0;
+  LaunchPlan plan;
   bool unstable = false;
   int32_t graph_k = 0;
   hipGraphExec_t gexec = nullptr;
@@ -86,20 +85,22 @@ int upload_desc(lbm_handle *h) {
   return LBM_OK;
 }
 
-int set_shape(lbm_handle *h, int shape) {
+int set_plan(lbm_handle *h, const LaunchPlan &plan) {
   int n;
   const TileShape *shapes = tile_shapes(&n);
-  if (shape < 0 || shape >= n) return LBM_EINVAL;
-  if (h->layout == LBM_LAYOUT_SINGLE && shape != 0) return LBM_EINVAL;
-  int32_t tx;
-  h->desc.tile_rows = marches(shapes[shape]) ? march_rows({launch_jet(h->cfg)}, shape) : 0;
-  h->desc.tile_steps = shapes[shape].steps;
-  h->ntiles = tiles_of(h->cfg.nx, h->cfg.nr, shape, h->desc.tile_rows, &tx);
-  h->grid = (h->ntiles + 7) / 8 * 8;
-  h->shape = shape;
-  h->desc.tiles_x = tx;
-  h->desc.ntiles = h->ntiles;
+  if (plan.shape < 0 || plan.shape >= n) return LBM_EINVAL;
+  if (h->layout == LBM_LAYOUT_SINGLE && plan.shape != 0) return LBM_EINVAL;
+  h->plan = plan;
+  fill_tiles(h->desc, plan,
+             marches(shapes[plan.shape]) ? march_rows({launch_jet(h->cfg)}, plan.shape) : 0);
   return upload_desc(h);
+}
+
+// Workgroups of a launch of one of the plan's shapes: one per tile.
+int grid_of(const lbm_handle *h, int shape) {
+  int n;
+  const int32_t tiles = tile_shapes(&n)[shape].steps > 2 ? h->desc.mtiles : h->desc.ntiles;
+  return (tiles + 7) / 8 * 8;
 }
 
 void drop_graph(lbm_handle *h) {
@@ -231,7 +232,9 @@ int create_common(const lbm_config *cfg, void *dev_buf, size_t bytes, void *stre
   std::vector<float4> rows;
   make_inlet(&h->cfg, 0, nullptr, nullptr, nullptr, rows);
   if ((rc = upload_inlet(h, rows, 1)) ||
-      (rc = set_shape(h, h->layout == LBM_LAYOUT_SINGLE ? 0 : default_tile_shape(h->prec, {launch_jet(*cfg)})))) {
+      (rc = set_plan(h, h->layout == LBM_LAYOUT_SINGLE
+                            ? LaunchPlan{0}
+                            : default_plan(h->prec, {launch_jet(*cfg)})))) {
     release(h);
     return rc;
   }
@@ -253,38 +256,32 @@ int create_common(const lbm_config *cfg, void *dev_buf, size_t bytes, void *stre
   return LBM_OK;
 }
 
-// One launch of one step: the in-place kernel for a single buffer, else the
-// handle's shape.
-int one_step(lbm_handle *h, int32_t koff, int32_t tog) {
-  if (h->layout == LBM_LAYOUT_SINGLE)
-    return launch_aa_step(h->prec, h->grid, h->stream, h->d_desc, nullptr, nullptr, koff,
-                          h->d_flag);
-  return launch_step(h->shape, h->prec, big_table(&h->cfg), h->grid, h->stream, h->d_desc,
-                     nullptr, nullptr, koff, tog, 1, h->d_flag);
-}
-
-// Steps one launch of the handle's shape advances.
+// Steps one launch of the handle's shape advances (the one shape of a single
+// buffer takes one).
 int32_t steps_per_launch(const lbm_handle *h) {
   int nsh;
-  return h->layout == LBM_LAYOUT_SINGLE ? 1 : tile_shapes(&nsh)[h->shape].steps;
+  return tile_shapes(&nsh)[h->plan.shape].steps;
 }
 
-// The launches of a group of k steps on `st`: with a shape of several steps
-// per launch, launches of that many and one of the rest, starting koff0
-// steps past the descriptor's step0 with its flip toggled by tog0; then, if
-// `advance`, the descriptor advance (koff0 = tog0 = 0 then).
+// Flip toggles of a group of k steps.
+int32_t toggles_of(const lbm_handle *h, int32_t k) {
+  return group_toggles(k, k, steps_per_launch(h), rest_steps(h->plan, k));
+}
+
+// The launches of a group of k steps on `st`, starting koff0 steps past the
+// descriptor's step0 with its flip toggled by tog0; then, if `advance`, the
+// descriptor advance (koff0 = tog0 = 0 then).
 int enqueue_group(lbm_handle *h, int32_t k, hipStream_t st, int32_t koff0 = 0, int32_t tog0 = 0,
                   bool advance = true) {
-  int rc = LBM_OK;
-  const int32_t spl = steps_per_launch(h);
-  for (int32_t q = 0; q < k && !rc; q += spl)
-    rc = h->layout == LBM_LAYOUT_SINGLE
-             ? launch_aa_step(h->prec, h->grid, st, h->d_desc, nullptr, nullptr, koff0 + q,
-                              h->d_flag)
-             : launch_step(h->shape, h->prec, big_table(&h->cfg), h->grid, st, h->d_desc,
-                           nullptr, nullptr, koff0 + q, tog0 ^ flip_toggles(q, spl),
-                           std::min(spl, k - q), h->d_flag);
-  if (!rc && advance) rc = launch_advance(st, h->d_desc, nullptr, 1, k, spl);
+  int rc = for_launches(h->plan, k, [&](int shape, int32_t q, int32_t tog, int32_t m) {
+    if (h->layout == LBM_LAYOUT_SINGLE)
+      return launch_aa_step(h->prec, grid_of(h, shape), st, h->d_desc, nullptr, nullptr, koff0 + q,
+                            h->d_flag);
+    return launch_step(shape, h->prec, big_table(&h->cfg), grid_of(h, shape), st, h->d_desc,
+                       nullptr, nullptr, koff0 + q, tog0 ^ tog, m, h->d_flag);
+  });
+  if (!rc && advance)
+    rc = launch_advance(st, h->d_desc, nullptr, 1, k, steps_per_launch(h), rest_steps(h->plan, k));
   return rc;
 }
 
@@ -302,7 +299,7 @@ int capture_group(lbm_handle *h, int32_t k) {
     return LBM_EDEVICE;
   }
   h->gexec_k = k;
-  h->gexec_shape = h->shape;
+  h->gexec_shape = h->plan.shape;
   return LBM_OK;
 }
 
@@ -310,7 +307,7 @@ int capture_group(lbm_handle *h, int32_t k) {
 // that the first lbm_step that replays it pays no capture or instantiation.
 int prepare_graph(lbm_handle *h) {
   if (h->graph_k <= 0) return LBM_OK;
-  if (h->gexec && h->gexec_k == h->graph_k && h->gexec_shape == h->shape) return LBM_OK;
+  if (h->gexec && h->gexec_k == h->graph_k && h->gexec_shape == h->plan.shape) return LBM_OK;
   drop_graph(h);
   const int rc = capture_group(h, h->graph_k);
   if (rc) return rc;
@@ -333,7 +330,7 @@ int prepare_graph(lbm_handle *h) {
 int catch_up(lbm_handle *h) {
   if (h->base == h->step && h->dflip == h->flip) return LBM_OK;
   const int rc = launch_advance(h->stream, h->d_desc, nullptr, 1, (int32_t)(h->step - h->base), 0,
-                                h->flip ^ h->dflip);
+                                0, h->flip ^ h->dflip);
   if (rc) return rc;
   h->base = h->step;
   h->dflip = h->flip;
@@ -348,17 +345,17 @@ int launch_steps(lbm_handle *h, int64_t n) {
     // (the lag is kept below 2^30 steps, so koff fits its 32 bits)
     if ((graph || h->step - h->base > (1 << 30)) && (rc = catch_up(h))) return rc;
     if (graph) {
-      if (!h->gexec || h->gexec_k != h->graph_k || h->gexec_shape != h->shape) {
+      if (!h->gexec || h->gexec_k != h->graph_k || h->gexec_shape != h->plan.shape) {
         drop_graph(h);
         if ((rc = capture_group(h, h->graph_k))) return rc;
       }
       LBM_HIP(hipGraphLaunch(h->gexec, h->stream));
       h->step += h->graph_k;
       h->base += h->graph_k;
-      h->flip ^= flip_toggles(h->graph_k, spl);
-      h->dflip ^= flip_toggles(h->graph_k, spl);
+      h->flip ^= toggles_of(h, h->graph_k);
+      h->dflip ^= toggles_of(h, h->graph_k);
       n -= h->graph_k;
-    } else if (spl > 1) {
+    } else {
       // the rest (fewer steps than a graph holds) as directly launched
       // steps: a graph's launches, offset from the descriptor, and no
       // advance (the device starts on the first kernel while the host
@@ -368,13 +365,8 @@ int launch_steps(lbm_handle *h, int64_t n) {
                               h->flip ^ h->dflip, false)))
         return rc;
       h->step += m;
-      h->flip ^= flip_toggles(m, spl);
+      h->flip ^= toggles_of(h, m);
       n -= m;
-    } else {
-      rc = one_step(h, (int32_t)(h->step - h->base), h->flip ^ h->dflip);
-      if (rc) return rc;
-      h->step += 1;
-      n -= 1;
     }
   }
   return LBM_OK;
@@ -495,7 +487,7 @@ int lbm_set_tile_shape(lbm_handle *h, int32_t index) {
   LBM_HIP(hipStreamSynchronize(h->stream));
   // (a refused index leaves the handle as it is: the device's descriptor may
   // lag behind the step count, and base and dflip say by how much)
-  const int rc = set_shape(h, index);
+  const int rc = set_plan(h, LaunchPlan{index});
   if (rc) return rc;
   drop_graph(h);
   return prepare_graph(h);

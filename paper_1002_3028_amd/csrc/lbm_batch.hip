@@ -36,7 +36,7 @@ namespace {
 struct Slot {
   bool used = false;
   int prec = LBM_PREC_FP32;  // the jet's storage form
-  int shape = 0;             // tile shape of its cohort (set by rebuild)
+  LaunchPlan plan;           // of its cohort (set by rebuild)
   lbm_config cfg{};
   std::vector<double> nu_tab, al_tab;
   JetDesc desc{};
@@ -126,7 +126,7 @@ struct lbm_batch {
   // its jets, the tile prefix sums and the header
   JetDesc *d_jets = nullptr;
   JetDesc *d_slot_desc = nullptr;  // per slot, for the single-jet helper kernels
-  int32_t *d_tiles = nullptr;
+  TileStart *d_tiles = nullptr;
   BatchHdr *d_hdr = nullptr;
   int32_t max_cohorts = 0;
   int32_t n_cohorts = 0;
@@ -165,23 +165,24 @@ struct lbm_batch {
   // that the uploads are asynchronous copies ordered before the launches; two
   // copies, as the device lists
   JetDesc *h_jets = nullptr;   // 2 x max_slots descriptors
-  int32_t *h_tiles = nullptr;  // 2 x (max_slots + max_cohorts) tile prefix sums
+  TileStart *h_tiles = nullptr;  // 2 x (max_slots + max_cohorts) tile prefix sums
   BatchHdr *h_hdr = nullptr;   // 2 x max_cohorts
   Scratch scratch;
   std::vector<int32_t> active;  // slots in the compact list, in order
   bool dirty = true;
   int shape = -1;       // -1: auto
   int32_t wg = 0;       // 0: auto
-  // storage form, tile shape and grid of each cohort of each copy of the
+  // storage form, launch plan and grids of each cohort of each copy of the
   // lists (set by rebuild)
   struct Cohort {
-    int prec = LBM_PREC_FP32, shape = 0;
-    int32_t grid = 0;
+    int prec = LBM_PREC_FP32;
+    LaunchPlan plan;
+    int32_t grid = 0, rest_grid = 0;
     bool big_table = false;  // a jet's property table exceeds the marching kernel's LDS copy
   };
   std::vector<Cohort> cohorts[2];
-  // (k, shape, grid, cohort, copy, storage form, big table)
-  std::map<std::tuple<int, int, int, int, int, int, bool>, hipGraphExec_t> graphs;
+  // (k, plan, grid, cohort, copy, storage form, big table)
+  std::map<std::tuple<int, int, int, int, int, int, int, int, bool>, hipGraphExec_t> graphs;
   // cohorts alternate between the batch's stream and a second one, so that
   // one cohort's launches fill the device while the other's start or drain
   static constexpr int MAX_STREAMS = 4;
@@ -193,16 +194,16 @@ struct lbm_batch {
 
 namespace {
 
-// The requested (or default) shape for a cohort.
-int pick_shape(const lbm_batch *b, int prec, const LaunchJets &jets) {
-  if (b->layout == LBM_LAYOUT_SINGLE) return 0;  // the in-place kernel's tiles
-  return b->shape >= 0 ? b->shape : default_tile_shape(prec, jets);
+// The requested (or default) shapes for a cohort.
+LaunchPlan pick_plan(const lbm_batch *b, int prec, const LaunchJets &jets) {
+  if (b->layout == LBM_LAYOUT_SINGLE) return LaunchPlan{0};  // the in-place kernel's tiles
+  return b->shape >= 0 ? LaunchPlan{b->shape} : default_plan(prec, jets);
 }
 
-// Steps one launch of a tile shape advances.
-int32_t steps_per_launch(const lbm_batch *b, int shape) {
+// Steps one launch of a plan's shape advances.
+int32_t steps_per_launch(const LaunchPlan &p) {
   int nsh;
-  return b->layout == LBM_LAYOUT_SINGLE ? 1 : tile_shapes(&nsh)[shape].steps;
+  return tile_shapes(&nsh)[p.shape].steps;
 }
 
 bool storage_form(int prec) {
@@ -223,7 +224,7 @@ void drop_graphs(lbm_batch *b) {
 // Pointers of copy `cp` of the cohort lists and of their staging.
 struct Lists {
   JetDesc *dj, *hj;
-  int32_t *dt, *ht;
+  TileStart *dt, *ht;
   BatchHdr *dh, *hh;
 };
 Lists lists_of(const lbm_batch *b, int32_t cp) {
@@ -295,7 +296,8 @@ int rebuild(lbm_batch *b) {
   for (size_t q = order.size(); q-- > 1;)
     later[q - 1] = later[q] + (b->slots[order[q]].prec != b->slots[order[q - 1]].prec ? 1 : 0);
   std::vector<std::vector<JetDesc>> jets(1);
-  std::vector<std::vector<int32_t>> start(1, std::vector<int32_t>(1, 0));
+  const std::vector<TileStart> none(1, TileStart{0, 0});
+  std::vector<std::vector<TileStart>> start(1, none);
   std::vector<size_t> bytes(1, 0);
   std::vector<lbm_batch::Cohort> meta(1);
   b->active.clear();
@@ -310,7 +312,7 @@ int rebuild(lbm_batch *b) {
                             (int32_t)jets.size() + later[q] < b->max_cohorts;
     if (other_form || full) {
       jets.emplace_back();
-      start.emplace_back(1, 0);
+      start.push_back(none);
       bytes.push_back(0);
       meta.emplace_back();
     }
@@ -328,13 +330,13 @@ int rebuild(lbm_batch *b) {
   for (size_t c = 0; c < jets.size(); ++c) {
     LaunchJets sizes;
     for (const JetDesc &d : jets[c]) sizes.push_back(launch_jet(d));
-    const int shape = meta[c].shape = pick_shape(b, meta[c].prec, sizes);
-    const int32_t rows = marches(shapes[shape]) ? march_rows(sizes, shape) : 0;
+    const LaunchPlan plan = meta[c].plan = pick_plan(b, meta[c].prec, sizes);
+    const int32_t rows = marches(shapes[plan.shape]) ? march_rows(sizes, plan.shape) : 0;
     for (JetDesc &d : jets[c]) {
-      b->slots[d.slot].shape = shape;
-      d.tile_rows = rows;
-      d.tile_steps = shapes[shape].steps;
-      start[c].push_back(start[c].back() + tiles_of(d.nx, d.nr, shape, rows, &d.tiles_x));
+      b->slots[d.slot].plan = plan;
+      fill_tiles(d, plan, rows);
+      const TileStart at = start[c].back();
+      start[c].push_back(TileStart{at.tiles + d.ntiles, at.mtiles + d.mtiles});
     }
   }
   // the groups that read this copy last, and the uploads from its staging
@@ -348,14 +350,14 @@ int rebuild(lbm_batch *b) {
   size_t jo = 0, to = 0;  // staging offsets
   for (int32_t c = 0; c < nh; ++c) {
     const int32_t n = c < b->n_cohorts ? (int32_t)jets[c].size() : 0;
-    L.hh[c] = BatchHdr{n, n > 0 ? start[c][n] : 0, {0, 0}};
+    L.hh[c] = n > 0 ? BatchHdr{n, start[c][n].tiles, start[c][n].mtiles, 0} : BatchHdr{};
     if (n > 0) std::memcpy(L.hj + jo, jets[c].data(), n * sizeof(JetDesc));
-    if (n > 0) std::memcpy(L.ht + to, start[c].data(), (n + 1) * sizeof(int32_t));
-    else L.ht[to] = 0;
+    if (n > 0) std::memcpy(L.ht + to, start[c].data(), (n + 1) * sizeof(TileStart));
+    else L.ht[to] = TileStart{0, 0};
     if (n > 0)
       LBM_HIP(hipMemcpyAsync(L.dj + (size_t)c * ms, L.hj + jo, n * sizeof(JetDesc),
                              hipMemcpyHostToDevice, b->stream));
-    LBM_HIP(hipMemcpyAsync(L.dt + (size_t)c * (ms + 1), L.ht + to, (n + 1) * sizeof(int32_t),
+    LBM_HIP(hipMemcpyAsync(L.dt + (size_t)c * (ms + 1), L.ht + to, (n + 1) * sizeof(TileStart),
                            hipMemcpyHostToDevice, b->stream));
     jo += n;
     to += n + 1;
@@ -368,9 +370,14 @@ int rebuild(lbm_batch *b) {
   // persistent grid of fixed size per cohort (graphs stay valid as jets come
   // and go): by default the workgroups the device holds at once
   for (lbm_batch::Cohort &m : meta) {
-    int32_t g = b->wg > 0 ? b->wg
-                          : resident_workgroups(m.shape, m.prec, b->layout == LBM_LAYOUT_SINGLE);
-    m.grid = (g + 7) / 8 * 8;
+    const auto grid = [&](int shape) {
+      const int32_t g = b->wg > 0 ? b->wg
+                                  : resident_workgroups(shape, m.prec,
+                                                        b->layout == LBM_LAYOUT_SINGLE);
+      return (g + 7) / 8 * 8;
+    };
+    m.grid = grid(m.plan.shape);
+    if (m.plan.rest >= 0) m.rest_grid = grid(m.plan.rest);
   }
   b->cohorts[cp] = meta;
   b->dirty = false;
@@ -381,29 +388,28 @@ int rebuild(lbm_batch *b) {
 // capture stream the first time).
 int run_group(lbm_batch *b, int32_t k, int32_t c, hipStream_t st) {
   const lbm_batch::Cohort &m = b->cohorts[b->copy][c];
-  const int shape = m.shape, prec = m.prec;
-  const int32_t grid = m.grid;
-  const int32_t spl = steps_per_launch(b, shape);
+  const int prec = m.prec;
   const int32_t ms = (int32_t)b->slots.size();
-  auto key = std::make_tuple((int)k, shape, (int)grid, (int)c, (int)b->copy, prec,
-                             m.big_table);
+  auto key = std::make_tuple((int)k, m.plan.shape, m.plan.rest, (int)m.plan.rest_max, (int)m.grid,
+                             (int)c, (int)b->copy, prec, m.big_table);
   auto it = b->graphs.find(key);
   if (it == b->graphs.end()) {
     const Lists L = lists_of(b, b->copy);
     JetDesc *jets = L.dj + (size_t)c * ms;
-    const int32_t *tiles = L.dt + (size_t)c * (ms + 1);
+    const TileStart *tiles = L.dt + (size_t)c * (ms + 1);
     const BatchHdr *hdr = L.dh + c;
     hipStream_t cs = b->cap;
     hipGraph_t g;
     LBM_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-    int rc = LBM_OK;
-    // launches of spl steps and one of the rest
-    for (int32_t q = 0; q < k && !rc; q += spl)
-      rc = b->layout == LBM_LAYOUT_SINGLE
-               ? launch_aa_step(prec, grid, cs, jets, tiles, hdr, q, b->d_flags)
-               : launch_step(shape, prec, m.big_table, grid, cs, jets, tiles, hdr, q,
-                             flip_toggles(q, spl), std::min(spl, k - q), b->d_flags);
-    if (!rc) rc = launch_advance(cs, jets, hdr, ms, k, spl);
+    int rc = for_launches(m.plan, k, [&](int shape, int32_t q, int32_t tog, int32_t n) {
+      const int32_t grid = shape == m.plan.shape ? m.grid : m.rest_grid;
+      return b->layout == LBM_LAYOUT_SINGLE
+                 ? launch_aa_step(prec, grid, cs, jets, tiles, hdr, q, b->d_flags)
+                 : launch_step(shape, prec, m.big_table, grid, cs, jets, tiles, hdr, q, tog, n,
+                               b->d_flags);
+    });
+    if (!rc)
+      rc = launch_advance(cs, jets, hdr, ms, k, steps_per_launch(m.plan), rest_steps(m.plan, k));
     const hipError_t e = hipStreamEndCapture(cs, &g);
     if (rc || e != hipSuccess) return rc ? rc : LBM_EDEVICE;
     hipGraphExec_t ex;
@@ -475,12 +481,12 @@ int lbm_batch_create(size_t budget_bytes, int32_t max_slots, int32_t precision,
   const size_t d_pool = part(nd, pooled * kBlockBytes);
   const size_t d_jets = part(nd, 2 * mc * ms * sizeof(JetDesc));
   const size_t d_slot = part(nd, ms * sizeof(JetDesc));
-  const size_t d_tiles = part(nd, 2 * mc * (ms + 1) * sizeof(int32_t));
+  const size_t d_tiles = part(nd, 2 * mc * (ms + 1) * sizeof(TileStart));
   const size_t d_hdr = part(nd, 2 * mc * sizeof(BatchHdr));
   const size_t h_pool = part(nh, pooled * kBlockBytes);
   const size_t h_jets = part(nh, 2 * ms * sizeof(JetDesc));
   const size_t h_slot = part(nh, ms * sizeof(JetDesc));
-  const size_t h_tiles = part(nh, 2 * (ms + mc) * sizeof(int32_t));
+  const size_t h_tiles = part(nh, 2 * (ms + mc) * sizeof(TileStart));
   const size_t h_hdr = part(nh, 2 * mc * sizeof(BatchHdr));
   const size_t h_flags = part(nh, ms * sizeof(int32_t));
   const size_t h_first = part(nh, kFirstResult);
@@ -491,11 +497,11 @@ int lbm_batch_create(size_t budget_bytes, int32_t max_slots, int32_t precision,
   if (ok) {
     b->d_jets = (JetDesc *)(b->d_mem + d_jets);
     b->d_slot_desc = (JetDesc *)(b->d_mem + d_slot);
-    b->d_tiles = (int32_t *)(b->d_mem + d_tiles);
+    b->d_tiles = (TileStart *)(b->d_mem + d_tiles);
     b->d_hdr = (BatchHdr *)(b->d_mem + d_hdr);
     b->h_jets = (JetDesc *)(b->h_mem + h_jets);
     b->h_slot = (JetDesc *)(b->h_mem + h_slot);
-    b->h_tiles = (int32_t *)(b->h_mem + h_tiles);
+    b->h_tiles = (TileStart *)(b->h_mem + h_tiles);
     b->h_hdr = (BatchHdr *)(b->h_mem + h_hdr);
     b->h_flags = (int32_t *)(b->h_mem + h_flags);
     b->first_result = b->h_mem + h_first;
@@ -528,11 +534,11 @@ int lbm_batch_create(size_t budget_bytes, int32_t max_slots, int32_t precision,
          hipEventCreateWithFlags(&b->start[q], hipEventDefault) == hipSuccess;
   if (ok) {
     std::memset(b->h_flags, 0, max_slots * sizeof(int32_t));
-    std::vector<BatchHdr> hz(2 * mc, BatchHdr{0, 0, {0, 0}});
-    std::vector<int32_t> tz(2 * mc * (max_slots + 1), 0);
+    std::vector<BatchHdr> hz(2 * mc, BatchHdr{});
+    std::vector<TileStart> tz(2 * mc * (max_slots + 1), TileStart{0, 0});
     ok = hipMemcpy(b->d_hdr, hz.data(), hz.size() * sizeof(BatchHdr), hipMemcpyHostToDevice) ==
              hipSuccess &&
-         hipMemcpy(b->d_tiles, tz.data(), tz.size() * sizeof(int32_t), hipMemcpyHostToDevice) ==
+         hipMemcpy(b->d_tiles, tz.data(), tz.size() * sizeof(TileStart), hipMemcpyHostToDevice) ==
              hipSuccess;
   }
   if (!ok) {
@@ -701,7 +707,7 @@ int lbm_batch_run(lbm_batch *b, int32_t k_steps) {
     Slot &sl = b->slots[s];
     if (sl.step >= sl.target) continue;
     const int64_t n = std::min<int64_t>(k_steps, sl.target - sl.step);
-    sl.flip ^= flip_toggles(n, steps_per_launch(b, sl.shape));
+    sl.flip ^= group_toggles(n, k_steps, steps_per_launch(sl.plan), rest_steps(sl.plan, k_steps));
     sl.step += n;
     if (sl.step >= sl.target) {
       sl.done_seq = b->seq;

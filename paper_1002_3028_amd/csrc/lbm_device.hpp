@@ -87,7 +87,9 @@ struct alignas(16) JetDesc {
   int64_t plane;           // elements per population plane (pitch * nr)
   int64_t step0;           // step count of the launch with koff = 0
   int64_t target;          // the jet stops at this step count
-  int32_t nx, nr, pitch, tiles_x;
+  int32_t nx, nr, pitch;
+  int32_t tiles_x, ntiles;         // tiles per row and of the jet in launches of one or two steps
+  int32_t mtiles_x, mtiles;        // and in launches of more
   int32_t n_t, table_n, hoop, slot;
   int32_t bc[4];
   float r0, nu0, alpha0, c18;      // c18 = 18 (C_s Delta)^2
@@ -95,8 +97,7 @@ struct alignas(16) JetDesc {
   float rho_ref, g4_ref;
   int32_t flip;                    // toggled by every launch that advances an even number of steps
   int32_t tile_rows;               // rows of one wave's tile (march_kernel)
-  int32_t ntiles;                  // tiles of the jet
-  int32_t tile_steps;              // steps a launch of its shape advances
+  int32_t tile_steps;              // steps a launch of more than two advances
   float wallT[4];                  // NaN: adiabatic
   float eq[4][4];                  // EQ side: rho, ux, ur, T
 };
@@ -109,30 +110,47 @@ __host__ __device__ inline int32_t flip_toggles(int64_t n, int32_t spl) {
   return (int32_t)(((n / spl) * (spl - 1) + (rest > 0 ? rest - 1 : 0)) & 1);
 }
 
-// Batch header in device memory: number of jets in the tile list and its
-// length.  The list itself is tile_start[0..njets] (prefix sums of the jets'
-// tile counts).
+// The same for the first n steps of a group of k, whose last launches, after
+// as many of spl steps as k holds, take up to rest_spl steps each.
+__host__ __device__ inline int32_t group_toggles(int64_t n, int32_t k, int32_t spl,
+                                                 int32_t rest_spl) {
+  const int32_t full = k - k % spl;
+  if (n <= full) return flip_toggles(n, spl);
+  return flip_toggles(full, spl) ^ flip_toggles(n - full, rest_spl);
+}
+
+// Batch header in device memory: number of jets in the tile lists and their
+// lengths.  The lists themselves are tile_start[0..njets] (prefix sums of the
+// jets' tile counts), for launches of one or two steps and for those of more:
+// a group may hold both.
 struct BatchHdr {
-  int32_t njets, ntiles;
-  int32_t pad[2];
+  int32_t njets, ntiles, mtiles;
+  int32_t pad;
+};
+struct TileStart {
+  int32_t tiles, mtiles;
 };
 
-// The jets of a launch.  A launch for one jet has no header and no tile list
-// (null): everything it needs is in the one descriptor, and a launch starts
-// two dependent loads earlier.
+// The jets of a launch (M: of more than two steps).  A launch for one jet has
+// no header and no tile list (null): everything it needs is in the one
+// descriptor, and a launch starts two dependent loads earlier.
+template <bool M>
 struct TileList {
   const JetDesc *jets;
-  const int32_t *tile_start;
+  const TileStart *tile_start;
   int32_t njets, ntiles;
-  __device__ __forceinline__ TileList(const JetDesc *j, const int32_t *ts, const BatchHdr *hdr)
+  __device__ __forceinline__ TileList(const JetDesc *j, const TileStart *ts, const BatchHdr *hdr)
       : jets(j), tile_start(ts) {
     if (hdr) {
       njets = hdr->njets;
-      ntiles = hdr->ntiles;
+      ntiles = M ? hdr->mtiles : hdr->ntiles;
     } else {
       njets = 1;
-      ntiles = j[0].ntiles;
+      ntiles = M ? j[0].mtiles : j[0].ntiles;
     }
+  }
+  __device__ __forceinline__ int32_t first(int32_t q) const {
+    return M ? tile_start[q].mtiles : tile_start[q].tiles;
   }
   // The jet of tile t, and t made the tile's number within it.
   __device__ __forceinline__ int32_t find(int32_t &t) const {
@@ -141,9 +159,9 @@ struct TileList {
       int32_t hi = njets - 1;
       while (lo < hi) {
         const int32_t mid = (lo + hi + 1) >> 1;
-        if (tile_start[mid] <= t) lo = mid; else hi = mid - 1;
+        if (first(mid) <= t) lo = mid; else hi = mid - 1;
       }
-      t -= tile_start[lo];
+      t -= first(lo);
     }
     return lo;
   }

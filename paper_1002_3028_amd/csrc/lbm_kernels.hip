@@ -8,16 +8,16 @@ namespace lbmx {
 // ---- kernels of no storage form ----------------------------------------------
 // Moves every jet's step0 by delta (clamped at the target); ends a captured
 // group of steps so that the same graph serves the next group.  The group's
-// launches took spl steps each and the last one the rest: flip_toggles of
-// them swapped the roles of a jet's buffers.  spl = 0: one jet, whose flip
-// is toggled by `flip`.
+// launches took spl steps each and the last ones up to rest_spl:
+// group_toggles of them swapped the roles of a jet's buffers.  spl = 0: one
+// jet, whose flip is toggled by `flip`.
 __global__ void advance_kernel(JetDesc *__restrict__ jets, const BatchHdr *__restrict__ hdr,
-                               int32_t delta, int32_t spl, int32_t flip) {
+                               int32_t delta, int32_t spl, int32_t rest_spl, int32_t flip) {
   const int32_t q = blockIdx.x * blockDim.x + threadIdx.x;
   if (q < (hdr ? hdr->njets : 1)) {
     const int64_t s0 = jets[q].step0, tg = jets[q].target;
     const int64_t s = s0 + delta < tg ? s0 + delta : tg;
-    jets[q].flip ^= spl > 0 ? flip_toggles(s - s0, spl) : flip;
+    jets[q].flip ^= spl > 0 ? group_toggles(s - s0, delta, spl, rest_spl) : flip;
     jets[q].step0 = s;
   }
 }
@@ -176,6 +176,8 @@ void fill_desc(JetDesc &d, const lbm_config *c) {
   d.rho_ref = (float)c->rho_ref;
   d.g4_ref = (float)(0.25 * c->g_ref);
   d.flip = 0;
+  d.tiles_x = d.mtiles_x = 1;
+  d.ntiles = d.mtiles = 0;
   d.tile_rows = 0;
   d.tile_steps = 1;
 }
@@ -283,13 +285,25 @@ const TileShape *tile_shapes(int *count) {
 // the two-step kernel in FP32 (2048 x 512 with four equilibrium sides: 13.7
 // against 17.0 us per step, 1024 x 512 between two walls: 8.6 against 8.8)
 // and one step in 16 bits (12.4 / 17.6, 7.7 / 10.1).
-int default_tile_shape(int prec, const LaunchJets &jets) {
+//
+// A launch of fewer steps than its shape holds costs more than its share (a
+// march of one step on 2048 x 512 takes 23.4 us, of two 30.3), so that a
+// group's last steps, or a caller's single ones, take another shape where that
+// is faster: after a march in FP32 one or two steps the two-step kernel (18.3
+// and 25.7 us; 4096 x 1024: 87 and 113 against 114 and 140; three steps 44.0
+// against 40.1, so they stay), in 16 bits the one-step kernel (FP16, one to
+// three steps on 2048 x 512: 11.9, 23.6, 35.5 against 23.5, 33.2, 46.1; beyond
+// the Infinity Cache two: 6000 x 1500, three steps 294 against 274); after
+// stacked rows one step the one-step kernel (128 x 32: 4.2 against 4.7; two
+// steps 7.7 against 5.7), after two rounds of them the two-step kernel (768 x
+// 192, one and two steps: 6.5 and 9.7 against 8.2 and 10.1).
+LaunchPlan default_plan(int prec, const LaunchJets &jets) {
   const bool fp32 = prec == LBM_PREC_FP32;
   const int cus = device_cus();
   int n, best = 0;
   const TileShape *s = tile_shapes(&n);
   double best_t = 1e30;
-  int64_t nodes = 0;
+  int64_t nodes = 0, best_rounds = 0;
   bool plain = true;
   for (const auto &j : jets) nodes += (int64_t)j.nx * j.nr, plain = plain && j.plain;
   const bool cached = 2 * NPOP * (fp32 ? 4 : 2) * nodes <= int64_t(256) << 20;
@@ -305,11 +319,12 @@ int default_tile_shape(int prec, const LaunchJets &jets) {
                                                    : 1.55;
   for (int q = 0; q < n; ++q) {
     const int k = s[q].steps;
+    int64_t rounds = 0;
     double t;
     if (s[q].stack_rows) {
       int64_t wg = 0;
       for (const auto &j : jets) wg += tiles_of(j.nx, j.nr, q, 0, nullptr);
-      const int64_t rounds = (wg + cus - 1) / cus;
+      rounds = (wg + cus - 1) / cus;
       if (!fp32 && rounds > 1) continue;
       t = (2.3 + rounds * (k <= 6 ? 3.0 + k : 10.5)) / k;
     } else if (fp32 && !plain && q == TWO_STEP) {
@@ -322,9 +337,32 @@ int default_tile_shape(int prec, const LaunchJets &jets) {
     } else {
       continue;
     }
-    if (t < best_t) best = q, best_t = t;
+    if (t < best_t) best = q, best_t = t, best_rounds = rounds;
   }
-  return best;
+  LaunchPlan plan{best};
+  if (s[best].steps > 2) {
+    const bool pair = fp32 && best_rounds != 1;
+    plan.rest = pair ? TWO_STEP : 0;
+    plan.rest_max = pair ? 2 : best_rounds ? 1 : cached || prec == LBM_PREC_FP16SR ? 3 : 2;
+  }
+  return plan;
+}
+
+int32_t rest_steps(const LaunchPlan &p, int32_t k) {
+  const int32_t spl = shapes()[p.shape].steps, rest = k % spl;
+  return rest > 0 && rest <= p.rest_max ? shapes()[p.rest].steps : spl;
+}
+
+void fill_tiles(JetDesc &d, const LaunchPlan &p, int32_t rows) {
+  d.tile_rows = rows;
+  d.tile_steps = shapes()[p.shape].steps;
+  d.tiles_x = d.mtiles_x = 1;
+  d.ntiles = d.mtiles = 0;
+  for (const int q : {p.rest, p.shape}) {
+    if (q < 0) continue;
+    if (shapes()[q].steps > 2) d.mtiles = tiles_of(d.nx, d.nr, q, rows, &d.mtiles_x);
+    else d.ntiles = tiles_of(d.nx, d.nr, q, 0, &d.tiles_x);
+  }
 }
 
 int tiles_of(int32_t nx, int32_t nr, int shape, int32_t rows, int32_t *tiles_x) {
@@ -376,7 +414,7 @@ int device_cus() {
 }
 
 int launch_step(int shape, int prec, bool big_table, int grid, hipStream_t st,
-                const JetDesc *jets, const int32_t *tiles, const BatchHdr *hdr, int32_t koff,
+                const JetDesc *jets, const TileStart *tiles, const BatchHdr *hdr, int32_t koff,
                 int32_t tog, int32_t nsteps, int32_t *flags) {
   const TileShape &s = shapes()[shape];
   const void *fn = (big_table && s.big[0] ? s.big : s.fn)[codec_index(prec)];
@@ -407,7 +445,7 @@ int resident_workgroups(int shape, int prec, bool single_buffer) {
   return (per_cu * cus + 7) / 8 * 8;
 }
 
-int launch_aa_step(int prec, int grid, hipStream_t st, const JetDesc *jets, const int32_t *tiles,
+int launch_aa_step(int prec, int grid, hipStream_t st, const JetDesc *jets, const TileStart *tiles,
                    const BatchHdr *hdr, int32_t koff, int32_t *flags) {
   int32_t tog = 0, nsteps = 1;
   void *args[] = {(void *)&jets, (void *)&tiles, (void *)&hdr,   (void *)&koff,
@@ -417,9 +455,10 @@ int launch_aa_step(int prec, int grid, hipStream_t st, const JetDesc *jets, cons
 }
 
 int launch_advance(hipStream_t st, JetDesc *jets, const BatchHdr *hdr, int32_t njets_max,
-                   int32_t delta, int32_t spl, int32_t flip) {
+                   int32_t delta, int32_t spl, int32_t rest_spl, int32_t flip) {
   const int blocks = (njets_max + 63) / 64;
-  hipLaunchKernelGGL(advance_kernel, dim3(blocks), dim3(64), 0, st, jets, hdr, delta, spl, flip);
+  hipLaunchKernelGGL(advance_kernel, dim3(blocks), dim3(64), 0, st, jets, hdr, delta, spl,
+                     rest_spl, flip);
   LBM_HIP(hipGetLastError());
   return LBM_OK;
 }

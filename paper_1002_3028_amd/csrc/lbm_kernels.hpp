@@ -86,14 +86,14 @@ __device__ __forceinline__ TileWalk tile_walk(int32_t ntiles) {
 // ---------------------------------------------------------------------------
 template <class C, int BX, int BY, int NY, int NX, int W, int CP>
 __global__ __launch_bounds__(BX *BY) __attribute__((amdgpu_waves_per_eu(W, 8))) void step_kernel(
-    const JetDesc *__restrict__ jets, const int32_t *__restrict__ tile_start,
+    const JetDesc *__restrict__ jets, const TileStart *__restrict__ tile_start,
     const BatchHdr *__restrict__ hdr, int32_t koff, int32_t tog, int32_t nsteps,
     int32_t *__restrict__ flags) {
   using T = typename C::T;
   constexpr int ES = (int)sizeof(T);
   constexpr int VB = ES * NX;  // bytes per lane per plane
   using VT = typename Pack<T, NX>::vec;
-  const TileList list(jets, tile_start, hdr);
+  const TileList<false> list(jets, tile_start, hdr);
   const TileWalk tw = tile_walk(list.ntiles);
   for (int32_t t = tw.first; t < tw.end; t += tw.stride) {
     int32_t lt = t;
@@ -302,7 +302,7 @@ struct LdsImage {
 // ---------------------------------------------------------------------------
 template <class C, int TY, int NW, int W, int CP>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(W, 8))) void pair_kernel(
-    const JetDesc *__restrict__ jets, const int32_t *__restrict__ tile_start,
+    const JetDesc *__restrict__ jets, const TileStart *__restrict__ tile_start,
     const BatchHdr *__restrict__ hdr, int32_t koff, int32_t tog, int32_t nsteps,
     int32_t *__restrict__ flags) {
   using T = typename C::T;
@@ -317,7 +317,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(W, 8)))
   static_assert(TY % NW == 0 && 2 * EH <= 64, "tile rows");
   __shared__ T img[(NPOP - P0) * EH * PAIR_W];
   const int lane = (int)threadIdx.x, wave = (int)threadIdx.y;
-  const TileList list(jets, tile_start, hdr);
+  const TileList<false> list(jets, tile_start, hdr);
   const TileWalk tw = tile_walk(list.ntiles);
   for (int32_t t = tw.first; t < tw.end; t += tw.stride) {
     int32_t lt = t;
@@ -502,13 +502,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(W, 8)))
 // ---------------------------------------------------------------------------
 template <class C>
 __global__ __launch_bounds__(256) void aa_kernel(
-    const JetDesc *__restrict__ jets, const int32_t *__restrict__ tile_start,
+    const JetDesc *__restrict__ jets, const TileStart *__restrict__ tile_start,
     const BatchHdr *__restrict__ hdr, int32_t koff, int32_t tog, int32_t nsteps,
     int32_t *__restrict__ flags) {
   using T = typename C::T;
   constexpr int ES = (int)sizeof(T);
   const int lane = (int)threadIdx.x, wave = (int)threadIdx.y;
-  const TileList list(jets, tile_start, hdr);
+  const TileList<false> list(jets, tile_start, hdr);
   const TileWalk tw = tile_walk(list.ntiles);
   for (int32_t t = tw.first; t < tw.end; t += tw.stride) {
     int32_t lt = t;

@@ -523,13 +523,13 @@ __device__ __forceinline__ bool march_tile(const JetDesc &jd, int64_t step, int3
 // ---------------------------------------------------------------------------
 template <class C, int K, int NW, int W, int CP, bool LT>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(W, 8))) void march_kernel(
-    const JetDesc *__restrict__ jets, const int32_t *__restrict__ tile_start,
+    const JetDesc *__restrict__ jets, const TileStart *__restrict__ tile_start,
     const BatchHdr *__restrict__ hdr, int32_t koff, int32_t tog, int32_t nsteps,
     int32_t *__restrict__ flags) {
   constexpr int HALO = K - 1, SW = 64 - 2 * HALO;
   __shared__ float4 table[LT ? MARCH_TABLE : 1];
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.y);
-  const TileList list(jets, tile_start, hdr);
+  const TileList<true> list(jets, tile_start, hdr);
   const TileWalk tw = tile_walk(list.ntiles);
   int32_t table_of = -1;
   for (int32_t t = tw.first; t < tw.end; t += tw.stride) {
@@ -554,8 +554,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(W, 8)))
       if (LT && tid < d.table_n) table[tid] = entry;
       __syncthreads();
     };
-    const int32_t ty = lt / d.tiles_x;
-    const int32_t tx = lt - ty * d.tiles_x;
+    const int32_t ty = lt / d.mtiles_x;
+    const int32_t tx = lt - ty * d.mtiles_x;
     const int i0 = tx * SW;
     const int j0 = (ty * NW + wave) * d.tile_rows;
     const int j1 = min(j0 + d.tile_rows, d.nr);

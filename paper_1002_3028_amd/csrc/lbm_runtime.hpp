@@ -78,8 +78,32 @@ LaunchJet launch_jet(const D &d) {
   for (int s = 0; s < 4; ++s) plain = plain && d.bc[s] != LBM_BC_EQ;
   return {d.nx, d.nr, plain};
 }
-// The shape of a launch over jets of one storage form.
-int default_tile_shape(int prec, const LaunchJets &jets);
+// The shapes of a group of launches: `shape` for as many steps as its launches
+// hold, and `rest` (if any) for what is left, if that is at most rest_max steps.
+struct LaunchPlan {
+  int shape = 0, rest = -1;
+  int32_t rest_max = 0;
+};
+// The plan for jets of one storage form.
+LaunchPlan default_plan(int prec, const LaunchJets &jets);
+// Steps per launch of what a group of k steps leaves after its full launches.
+int32_t rest_steps(const LaunchPlan &p, int32_t k);
+// A jet's tiles in the plan's launches (rows: the marching kernel's tile_rows).
+void fill_tiles(JetDesc &d, const LaunchPlan &p, int32_t rows);
+// launch(shape, offset in the group, flip toggles before it, steps) for every
+// launch of a group of k steps, up to the first that fails.
+template <class F>
+int for_launches(const LaunchPlan &p, int32_t k, const F &launch) {
+  int n, rc = 0;
+  const TileShape *s = tile_shapes(&n);
+  const int32_t spl = s[p.shape].steps, rest_spl = rest_steps(p, k);
+  for (int32_t q = 0, m = 0; q < k && !rc; q += m) {
+    const int shape = k - q < spl && k - q <= p.rest_max ? p.rest : p.shape;
+    m = std::min(s[shape].steps, k - q);
+    rc = launch(shape, q, group_toggles(q, k, spl, rest_spl), m);
+  }
+  return rc;
+}
 inline bool marches(const TileShape &s) { return s.big[0] != nullptr && s.stack_rows == 0; }
 
 inline int codec_index(int prec) { return prec - LBM_PREC_FP32; }
@@ -89,14 +113,14 @@ inline int codec_index(int prec) { return prec - LBM_PREC_FP32; }
 // steps it may take (at most the shape's); big_table: a jet's property table
 // has more entries than the marching kernel holds in LDS.
 int launch_step(int shape, int prec, bool big_table, int grid, hipStream_t st, const JetDesc *jets,
-                const int32_t *tiles, const BatchHdr *hdr, int32_t koff, int32_t tog,
+                const TileStart *tiles, const BatchHdr *hdr, int32_t koff, int32_t tog,
                 int32_t nsteps, int32_t *flags);
-// Advance after a group of delta steps in launches of spl steps and one of
-// the rest (spl = 0: one jet, its flip toggled by `flip`).
+// Advance after a group of delta steps in launches of spl steps and, of the
+// rest, rest_spl (spl = 0: one jet, its flip toggled by `flip`).
 int launch_advance(hipStream_t st, JetDesc *jets, const BatchHdr *hdr, int32_t njets_max,
-                   int32_t delta, int32_t spl, int32_t flip = 0);
+                   int32_t delta, int32_t spl, int32_t rest_spl, int32_t flip = 0);
 // Single-buffer step over shape 0's tile list.
-int launch_aa_step(int prec, int grid, hipStream_t st, const JetDesc *jets, const int32_t *tiles,
+int launch_aa_step(int prec, int grid, hipStream_t st, const JetDesc *jets, const TileStart *tiles,
                    const BatchHdr *hdr, int32_t koff, int32_t *flags);
 // Helpers on the state after `step` steps, seen through `view`
 // (state_view_of).

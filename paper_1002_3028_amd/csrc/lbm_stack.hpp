@@ -42,7 +42,7 @@ enum : int { TILE_INNER = 0, TILE_JET = 1, TILE_ANY = 2 };
 // ---------------------------------------------------------------------------
 template <class C, bool LT>
 __global__ __launch_bounds__(64 * STACK_ROWS) void stack_kernel(
-    const JetDesc *__restrict__ jets, const int32_t *__restrict__ tile_start,
+    const JetDesc *__restrict__ jets, const TileStart *__restrict__ tile_start,
     const BatchHdr *__restrict__ hdr, int32_t koff, int32_t tog, int32_t nsteps,
     int32_t *__restrict__ flags) {
   using T = typename C::T;
@@ -53,7 +53,7 @@ __global__ __launch_bounds__(64 * STACK_ROWS) void stack_kernel(
   const int lane = (int)threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.y);
   const int tid = lane + 64 * wave;
-  const TileList list(jets, tile_start, hdr);
+  const TileList<true> list(jets, tile_start, hdr);
   const TileWalk tw = tile_walk(list.ntiles);
   int32_t table_of = -1;
   for (int32_t t = tw.first; t < tw.end; t += tw.stride) {
@@ -68,8 +68,8 @@ __global__ __launch_bounds__(64 * STACK_ROWS) void stack_kernel(
     if (left < m) m = (int)left;
     const Physics ph(d);
     const int nx = d.nx, nr = d.nr;
-    const int32_t ty = lt / d.tiles_x;
-    const int32_t tx = lt - ty * d.tiles_x;
+    const int32_t ty = lt / d.mtiles_x;
+    const int32_t tx = lt - ty * d.mtiles_x;
     const int sw = 64 - 2 * halo, sh = STACK_ROWS - 2 * halo;
     const int i0 = tx * sw, j0 = ty * sh, j1 = min(j0 + sh, nr);
     const int i = i0 - halo + lane, j = j0 - halo + wave;
