@@ -60,8 +60,17 @@ constexpr int32_t kPoolSlots = 512;
 // columns and rows together.
 constexpr size_t kFirstResult = size_t(64) << 10;
 
-// Population buffers from which jets of one cohort are split over the streams.
+// Population buffers from which jets of one cohort are split over the streams,
+// and how many times them (bytes by steps of a group) a group has to be worth:
+// the second stream costs a group 25 to 40 us, which a short one does not win
+// back.  One cohort / split, us per group: 16 FP16 jets of 66 MiB 36 / 72 for
+// one step, 97 / 102 for 5, 171 / 160 for 10, 766 / 640 for 50; 4 of 59 MiB
+// 120 / 122 for 7; FP16SR 8 of 53 MiB 150 / 150 for 10.  In FP32, where one
+// cohort marches several steps per launch too: 4 jets of 118 MiB 41 / 73, 204 /
+// 240 for 20, 40 of 35 MiB 30 / 73, 221 / 216 for 50; serving sets, whose jets
+// come and go in groups of 100, gain (6 of 53 MiB 2.37 / 1.97 ms).
 constexpr size_t kSplitBytes = size_t(32) << 20;
+size_t split_work(int prec) { return size_t(prec == LBM_PREC_FP32 ? 2048 : 512) << 20; }
 struct SlotBlock {
   void *p = nullptr;  // device
   void *h = nullptr;  // pinned host staging of the same size (the upload is
@@ -170,6 +179,13 @@ struct lbm_batch {
   Scratch scratch;
   std::vector<int32_t> active;  // slots in the compact list, in order
   bool dirty = true;
+  // whether a group's length decides if the jets are split over the streams
+  // (then their buffers' bytes, else 0), what was decided, and how many runs
+  // in a row would have it otherwise: the second shares the jets out anew, so
+  // that one odd run among others of a length does not
+  size_t open_bytes = 0;
+  bool is_split = false;
+  int32_t otherwise = 0;
   int shape = -1;       // -1: auto
   int32_t wg = 0;       // 0: auto
   // storage form, launch plan and grids of each cohort of each copy of the
@@ -238,12 +254,16 @@ Lists lists_of(const lbm_batch *b, int32_t cp) {
 // stream, the largest first, each to the lightest cohort: the cohort of each,
 // *order then sorted by it.  Empty if they are filled up one after another
 // instead: several forms, more than the streams' cohorts may hold together, or
-// so little that a launch's work is smaller than its fixed part.  Cohorts on
+// so little that a launch's (or, in one cohort, the group's) work is smaller
+// than its fixed part; b->open_bytes and is_split say which.  Cohorts on
 // two streams overlap each other's launches and tails, which a set that fits
 // one cohort, or one and a bit, would not (FP16SR, admission to last profile:
 // 8 jets of 79 MiB 4.2 -> 3.2 ms, 4 jets of 48 MiB 3.6 -> 3.0; 6 of 23 MiB
 // 2.65 and 2.70).
-std::vector<int32_t> split_evenly(const lbm_batch *b, std::vector<int32_t> *order) {
+std::vector<int32_t> split_evenly(lbm_batch *b, std::vector<int32_t> *order, int32_t k_steps) {
+  b->open_bytes = 0;
+  b->is_split = false;
+  b->otherwise = 0;
   const size_t n = order->size(), k = std::min<size_t>(b->nstreams, b->max_cohorts);
   size_t total = 0;
   for (int32_t s : *order) {
@@ -252,6 +272,11 @@ std::vector<int32_t> split_evenly(const lbm_batch *b, std::vector<int32_t> *orde
   }
   if (n < 2 || k < 2 || !b->cohort_bytes || total < kSplitBytes || total > k * b->cohort_bytes)
     return {};
+  if (total <= b->cohort_bytes) {
+    b->open_bytes = total;
+    b->is_split = total * k_steps >= split_work(b->slots[order->front()].prec);
+    if (!b->is_split) return {};
+  }
   std::vector<int32_t> large = *order;
   std::stable_sort(large.begin(), large.end(), [&](int32_t x, int32_t y) {
     return b->slots[x].bytes > b->slots[y].bytes;
@@ -275,8 +300,8 @@ std::vector<int32_t> split_evenly(const lbm_batch *b, std::vector<int32_t> *orde
 // first), in slot order within a form; a new cohort at every change of form
 // and whenever the next jet's buffers would take the cohort past
 // cohort_bytes.  Written into the copy of the lists that the groups in
-// flight do not read.
-int rebuild(lbm_batch *b) {
+// flight do not read.  For runs of k_steps.
+int rebuild(lbm_batch *b, int32_t k_steps) {
   const int32_t ms = (int32_t)b->slots.size();
   std::vector<int32_t> order;
   for (int32_t s = 0; s < ms; ++s)
@@ -288,7 +313,7 @@ int rebuild(lbm_batch *b) {
   };
   std::stable_sort(order.begin(), order.end(),
                    [&](int32_t x, int32_t y) { return form_key(x) < form_key(y); });
-  const std::vector<int32_t> part = split_evenly(b, &order);
+  const std::vector<int32_t> part = split_evenly(b, &order, k_steps);
   // storage forms after each position's own (cohorts kept for them: a form
   // change always opens a cohort; max_cohorts >= the forms present, since it
   // is at least min(max_slots, 64))
@@ -679,7 +704,13 @@ int lbm_batch_run(lbm_batch *b, int32_t k_steps) {
   if (!b || k_steps < 0) return LBM_EINVAL;
   if (k_steps == 0) return LBM_OK;
   int rc;
-  if (b->dirty && (rc = rebuild(b))) return rc;
+  if (!b->dirty && b->open_bytes) {
+    const bool split =
+        b->open_bytes * k_steps >= split_work(b->slots[b->active.front()].prec);
+    b->otherwise = split != b->is_split ? b->otherwise + 1 : 0;
+    if (b->otherwise > 1) b->dirty = true;
+  }
+  if (b->dirty && (rc = rebuild(b, k_steps))) return rc;
   if (b->active.empty()) return LBM_OK;
   ++b->queued;
   LBM_HIP(hipEventRecord(b->start[b->seq % lbm_batch::RING], b->stream));

@@ -66,3 +66,40 @@ def test_cohorts_follow_the_number_of_streams():
             ref = s.moments()
         for key in ref:
             assert np.array_equal(m[key], ref[key]), (p["nx"], key)
+
+
+def test_short_groups_run_as_one_cohort():
+    """Jets that one cohort holds are split over two streams only for groups
+    worth it, from the second run in a row on."""
+    from paper_1002_3028_amd import lbm
+    with lbm.Batch(1 << 28, 8, "fp16") as b:
+        for p, inlet in _uneven():
+            b.admit(p, inlet, 1 << 40)
+        assert _launches(b, 2)[0] == 1
+        assert _launches(b, 20)[0] == 2  # (two runs of 20)
+        b.run(2)
+        b.run(20)
+        assert _launches(b, 20)[0] == 2
+        b.run(2)
+        assert _launches(b, 2)[0] == 1
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp16", "fp16sr"])
+def test_regrouped_jets_keep_their_bits(precision):
+    """Runs of lengths that change how the jets are shared out, while one after
+    another stops: each jet equals itself alone with one step per launch."""
+    from paper_1002_3028_amd import lbm
+    jets = [(p, inlet, 40 + 61 * q) for q, (p, inlet) in enumerate(_uneven())]
+    with lbm.Batch(1 << 28, 8, precision) as b:
+        slots = [b.admit(*j) for j in jets]
+        for k in (1, 2, 60, 60, 3, 2, 1, 70, 70, 70, 5, 5, 1, 1):
+            b.run(k)
+        assert [b.poll(s) for s in slots] == [n for _, _, n in jets]
+        got = [b.moments(s) for s in slots]
+    for (p, inlet, n), m in zip(jets, got):
+        with lbm.Solver(p, precision, tile_shape=0) as s:
+            s.set_inlet(*inlet)
+            s.step(n)
+            ref = s.moments()
+        for key in ref:
+            assert np.array_equal(m[key], ref[key]), (p["nx"], n, key)
