@@ -98,6 +98,7 @@ struct alignas(16) JetDesc {
   int32_t flip;                    // toggled by every launch that advances an even number of steps
   int32_t tile_rows;               // rows of one wave's tile (march_kernel)
   int32_t tile_steps;              // steps a launch of more than two advances
+  int32_t cus;                     // of the device: workgroups of one filling (march_kernel)
   float wallT[4];                  // NaN: adiabatic
   float eq[4][4];                  // EQ side: rho, ux, ur, T
 };

@@ -180,6 +180,7 @@ void fill_desc(JetDesc &d, const lbm_config *c) {
   d.ntiles = d.mtiles = 0;
   d.tile_rows = 0;
   d.tile_steps = 1;
+  d.cus = device_cus();
 }
 
 int make_inlet(const lbm_config *c, int32_t n_t, const double *ux, const double *ur,

@@ -498,7 +498,7 @@ __device__ __forceinline__ bool march_tile(const JetDesc &jd, int64_t step, int3
 // state is larger than the caches: 29.9 us on 4096 x 1024.  W = 2 waves per SIMD: the
 // levels' rows need 190 VGPRs, and held to 128 the kernel spills.
 //
-// The workgroups fill the 256 CUs once before a second goes on each.  Of two
+// The workgroups fill the CUs once before a second goes on each.  Of two
 // waves on a SIMD the older issues first, so that it would be done after
 // 22 us of a 2048 x 512 launch and leave the younger 10 us alone, in which
 // the SIMD can fill only two thirds of its issue slots.  The workgroups of
@@ -564,7 +564,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(W, 8)))
       table_of = jid;
       continue;
     }
-    const bool late = ((blockIdx.x >> 8) & 1) != 0;
+    const bool late = ((blockIdx.x / (uint32_t)d.cus) & 1) != 0;
     const bool px = d.bc[0] == BC_PERIODIC;
     const bool left_edge = !px & (i0 == 0), right_edge = !px & (d.nx <= i0 - HALO + 63);
     bool ok;
