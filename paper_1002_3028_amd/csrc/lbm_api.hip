@@ -86,13 +86,8 @@ int upload_desc(lbm_handle *h) {
 }
 
 int set_plan(lbm_handle *h, const LaunchPlan &plan) {
-  int n;
-  const TileShape *shapes = tile_shapes(&n);
-  if (plan.shape < 0 || plan.shape >= n) return LBM_EINVAL;
-  if (h->layout == LBM_LAYOUT_SINGLE && plan.shape != 0) return LBM_EINVAL;
   h->plan = plan;
-  fill_tiles(h->desc, plan,
-             marches(shapes[plan.shape]) ? march_rows({launch_jet(h->cfg)}, plan.shape) : 0);
+  fill_tiles(h->desc, plan);
   return upload_desc(h);
 }
 
@@ -487,7 +482,10 @@ int lbm_set_tile_shape(lbm_handle *h, int32_t index) {
   LBM_HIP(hipStreamSynchronize(h->stream));
   // (a refused index leaves the handle as it is: the device's descriptor may
   // lag behind the step count, and base and dflip say by how much)
-  const int rc = set_plan(h, LaunchPlan{index});
+  int n;
+  tile_shapes(&n);
+  if (index < 0 || index >= n || (h->layout == LBM_LAYOUT_SINGLE && index != 0)) return LBM_EINVAL;
+  const int rc = set_plan(h, plan_of(index, {launch_jet(h->cfg)}));
   if (rc) return rc;
   drop_graph(h);
   return prepare_graph(h);

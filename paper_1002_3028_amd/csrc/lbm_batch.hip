@@ -213,7 +213,7 @@ namespace {
 // The requested (or default) shapes for a cohort.
 LaunchPlan pick_plan(const lbm_batch *b, int prec, const LaunchJets &jets) {
   if (b->layout == LBM_LAYOUT_SINGLE) return LaunchPlan{0};  // the in-place kernel's tiles
-  return b->shape >= 0 ? LaunchPlan{b->shape} : default_plan(prec, jets);
+  return b->shape >= 0 ? plan_of(b->shape, jets) : default_plan(prec, jets);
 }
 
 // Steps one launch of a plan's shape advances.
@@ -350,16 +350,13 @@ int rebuild(lbm_batch *b, int32_t k_steps) {
     b->active.push_back(s);
   }
   // the cohorts' tile lists
-  int nsh;
-  const TileShape *shapes = tile_shapes(&nsh);
   for (size_t c = 0; c < jets.size(); ++c) {
     LaunchJets sizes;
     for (const JetDesc &d : jets[c]) sizes.push_back(launch_jet(d));
     const LaunchPlan plan = meta[c].plan = pick_plan(b, meta[c].prec, sizes);
-    const int32_t rows = marches(shapes[plan.shape]) ? march_rows(sizes, plan.shape) : 0;
     for (JetDesc &d : jets[c]) {
       b->slots[d.slot].plan = plan;
-      fill_tiles(d, plan, rows);
+      fill_tiles(d, plan);
       const TileStart at = start[c].back();
       start[c].push_back(TileStart{at.tiles + d.ntiles, at.mtiles + d.mtiles});
     }

@@ -305,6 +305,7 @@ LaunchPlan default_plan(int prec, const LaunchJets &jets) {
   const TileShape *s = tile_shapes(&n);
   double best_t = 1e30;
   int64_t nodes = 0, best_rounds = 0;
+  int32_t best_rows = 0;
   bool plain = true;
   for (const auto &j : jets) nodes += (int64_t)j.nx * j.nr, plain = plain && j.plain;
   const bool cached = 2 * NPOP * (fp32 ? 4 : 2) * nodes <= int64_t(256) << 20;
@@ -321,6 +322,7 @@ LaunchPlan default_plan(int prec, const LaunchJets &jets) {
   for (int q = 0; q < n; ++q) {
     const int k = s[q].steps;
     int64_t rounds = 0;
+    int32_t rows = 0;
     double t;
     if (s[q].stack_rows) {
       int64_t wg = 0;
@@ -330,17 +332,17 @@ LaunchPlan default_plan(int prec, const LaunchJets &jets) {
       t = (2.3 + rounds * (k <= 6 ? 3.0 + k : 10.5)) / k;
     } else if (fp32 && !plain && q == TWO_STEP) {
       t = 4.3 + 8.9e-6 * nodes;
-    } else if (marches(s[q]) && plain && k == (fp32 && !cached ? 5 : 4)) {
+    } else if (marches(s[q]) && plain && one_step > 0.0 && k == (fp32 && !cached ? 5 : 4)) {
       double us;
-      march_rows(jets, q, &us);
+      rows = march_rows(jets, q, &us);
       t = (5.5 + weight * us) / k;
       if (t >= one_step) continue;
     } else {
       continue;
     }
-    if (t < best_t) best = q, best_t = t, best_rounds = rounds;
+    if (t < best_t) best = q, best_t = t, best_rounds = rounds, best_rows = rows;
   }
-  LaunchPlan plan{best};
+  LaunchPlan plan{best, -1, 0, best_rows};
   if (s[best].steps > 2) {
     const bool pair = fp32 && best_rounds != 1;
     plan.rest = pair ? TWO_STEP : 0;
@@ -354,14 +356,18 @@ int32_t rest_steps(const LaunchPlan &p, int32_t k) {
   return rest > 0 && rest <= p.rest_max ? shapes()[p.rest].steps : spl;
 }
 
-void fill_tiles(JetDesc &d, const LaunchPlan &p, int32_t rows) {
-  d.tile_rows = rows;
+LaunchPlan plan_of(int shape, const LaunchJets &jets) {
+  return {shape, -1, 0, marches(shapes()[shape]) ? march_rows(jets, shape) : 0};
+}
+
+void fill_tiles(JetDesc &d, const LaunchPlan &p) {
+  d.tile_rows = p.rows;
   d.tile_steps = shapes()[p.shape].steps;
   d.tiles_x = d.mtiles_x = 1;
   d.ntiles = d.mtiles = 0;
   for (const int q : {p.rest, p.shape}) {
     if (q < 0) continue;
-    if (shapes()[q].steps > 2) d.mtiles = tiles_of(d.nx, d.nr, q, rows, &d.mtiles_x);
+    if (shapes()[q].steps > 2) d.mtiles = tiles_of(d.nx, d.nr, q, p.rows, &d.mtiles_x);
     else d.ntiles = tiles_of(d.nx, d.nr, q, 0, &d.tiles_x);
   }
 }

@@ -79,17 +79,19 @@ LaunchJet launch_jet(const D &d) {
   return {d.nx, d.nr, plain};
 }
 // The shapes of a group of launches: `shape` for as many steps as its launches
-// hold, and `rest` (if any) for what is left, if that is at most rest_max steps.
+// hold, and `rest` (if any) for what is left, if that is at most rest_max
+// steps; rows of a wave's tile where `shape` marches.
 struct LaunchPlan {
   int shape = 0, rest = -1;
-  int32_t rest_max = 0;
+  int32_t rest_max = 0, rows = 0;
 };
-// The plan for jets of one storage form.
+// The plan for jets of one storage form, and the plan of one given shape.
 LaunchPlan default_plan(int prec, const LaunchJets &jets);
+LaunchPlan plan_of(int shape, const LaunchJets &jets);
 // Steps per launch of what a group of k steps leaves after its full launches.
 int32_t rest_steps(const LaunchPlan &p, int32_t k);
-// A jet's tiles in the plan's launches (rows: the marching kernel's tile_rows).
-void fill_tiles(JetDesc &d, const LaunchPlan &p, int32_t rows);
+// A jet's tiles in the plan's launches.
+void fill_tiles(JetDesc &d, const LaunchPlan &p);
 // launch(shape, offset in the group, flip toggles before it, steps) for every
 // launch of a group of k steps, up to the first that fails.
 template <class F>
