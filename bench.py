@@ -11,16 +11,19 @@ cost.
 Throughput (`value`) is GLUPS, lattice node updates per second / 1e9, from
 that wall clock.
 
-`roofline`: HBM bandwidth at the algorithmic 104 B per node update for FP32
-storage (13 populations read and written) and 52 B for 16-bit storage.
-`achieved` = those bytes times the node updates of one launch, divided by
-the launch duration, from HIP events on the solver's stream around the step
-launches of the timed region (`event_us_per_launch`).  The average duration
+`roofline`: what bounds the kernel.  With one step per launch HBM bandwidth,
+at the algorithmic 104 B per node update for FP32 storage (13 populations read
+and written) and 52 B for 16-bit storage: `achieved` = those bytes times the
+node updates of one launch, divided by the launch duration, from HIP events on
+the solver's stream around the step launches of the timed region
+(`event_us_per_launch`).  A launch of m steps updates each node m times while
+reading and writing each population once, so that this rate is no bandwidth:
+it is given as `effective_GBps`, and the bound is the larger of the vector-ALU
+issue that the counters show (`alu`) and HBM bandwidth by the bytes that one
+launch moves (`traffic`, from the rocprofv3 counters in a committed summary;
+without one, each population read and written once).  The average duration
 of the same kernel in the committed rocprofv3 summary is given beside it
-(`rocprof_us_per_launch`).  A launch of m steps updates each node m times while
-reading and writing each population once; `traffic` is the HBM bytes one
-launch moves by the rocprofv3 counters (committed summary), and
-`traffic_GBps` their rate.
+(`rocprof_us_per_launch`).
 
 Prints one JSON line.  Extras: one step per launch, FP16 / BF16 / FP16SR
 storage on the same jet, the 4096 x 1024 jet (a working set above the
@@ -199,25 +202,33 @@ def time_jet(params, inlet, precision, steps, warmup, check_every=1000, tile_sha
 
 
 def roofline_block(prec, info, nodes, ms_step, traffic_name, trace_name=None, tag=None):
-    """HBM roofline of the dominant kernel: algorithmic bytes per launch over
-    the launch duration from HIP events (steps only, graph replays)."""
+    """Roofline of the dominant kernel over the launch duration from HIP events
+    (steps only, graph replays): HBM by the algorithmic bytes with one step per
+    launch, else by the bytes moved or vector-ALU issue, whichever is closer
+    to its peak."""
     kernel = kernel_of(info)
     ms_launch = ms_step * info["steps"]
     updates = nodes * info["steps"]
     alg = BYTES_PER_NODE[prec] * updates
-    achieved = alg / (ms_launch * 1e-3) / 1e9
+    effective = alg / (ms_launch * 1e-3) / 1e9
     traffic = read_traffic(traffic_name) if traffic_name else None
+    moved = traffic or BYTES_PER_NODE[prec] * nodes
+    achieved = (effective if info["steps"] == 1 else moved / (ms_launch * 1e-3) / 1e9)
     out = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
            "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic, "kernel": kernel,
            "steps_per_launch": info["steps"], "node_updates_per_launch": updates,
            "bytes_per_node_update": BYTES_PER_NODE[prec],
            "algorithmic_bytes_per_launch": alg,
+           "effective_GBps": round(effective, 1),
            "event_us_per_launch": round(ms_launch * 1e3, 3),
            "rocprof_us_per_launch": (read_trace_us(trace_name, f"{kernel}<lbmx::{CODEC[prec]}")
                                      if trace_name else None),
            "traffic_GBps": (round(traffic / (ms_launch * 1e-3) / 1e9, 1) if traffic else None)}
     if tag:
-        out["alu"] = alu_roofline(kernel, prec, tag, nodes, ms_step)
+        alu = out["alu"] = alu_roofline(kernel, prec, tag, nodes, ms_step)
+        if info["steps"] > 1 and (alu["frac"] or 0) > out["frac"]:
+            out.update(bound="valu", achieved=alu["achieved"], peak=alu["peak"],
+                       unit=alu["unit"], frac=alu["frac"])
     return out
 
 
@@ -482,12 +493,12 @@ def main():
         steps_x = max(200, args.steps // 4)
         warm_x = max(10, args.warmup // 2)
 
-        def entry(prec, q, t, n_nodes, n_steps, traffic_name=None, trace_name=None):
+        def entry(prec, q, t, n_nodes, n_steps, traffic_name=None, trace_name=None, tag=None):
             inf = lbm.tile_shape_info(q)
             e = {"glups": round(n_nodes * n_steps / t["wall_s"] / 1e9, 3), "tile_shape": inf,
                  "event_glups": round(n_nodes / (t["event_ms_per_step"] * 1e-3) / 1e9, 3)}
             e["roofline"] = roofline_block(prec, inf, n_nodes, t["event_ms_per_step"],
-                                           traffic_name, trace_name)
+                                           traffic_name, trace_name, tag)
             return e
 
         # the same jet with one step per launch (the best one-step shape)
@@ -501,7 +512,8 @@ def main():
             tt = time_jet(p, inlet, prec, steps_x, warm_x, tile_shape=q)
             kind = kernel_of(lbm.tile_shape_info(q)).split("_")[0]
             extra[f"{prec}_2048x512"] = entry(prec, q, tt, nodes, steps_x,
-                                              f"traffic_{kind}_{prec}_2048x512.txt")
+                                              f"traffic_{kind}_{prec}_2048x512.txt",
+                                              tag="2048x512")
         # the 4096 x 1024 jet: its FP32 buffers (436 MB) exceed the Infinity
         # Cache, so this is the HBM-bandwidth case
         pl, inl, _ = inputs.workload_large(n_t=4000)
