@@ -60,6 +60,12 @@ constexpr int32_t kPoolSlots = 512;
 // columns and rows together.
 constexpr size_t kFirstResult = size_t(64) << 10;
 
+// Graphs kept at most.  A group is captured when its length, cohort and plan
+// first come together, and the plan follows the cohort's jets, so that a jet's
+// end can bring a new one: 12 to 58 us for 20 to 100 FP32 steps, 18 to 175 in
+// FP16SR (one node a step 35 to 106 and 51 to 169).
+constexpr size_t kMaxGraphs = 256;
+
 // Population buffers from which jets of one cohort are split over the streams,
 // and how many times them (bytes by steps of a group) a group has to be worth:
 // the second stream costs a group 25 to 40 us, which a short one does not win
@@ -422,6 +428,12 @@ int run_group(lbm_batch *b, int32_t k, int32_t c, hipStream_t st) {
     const BatchHdr *hdr = L.dh + c;
     hipStream_t cs = b->cap;
     hipGraph_t g;
+    if (b->graphs.size() >= kMaxGraphs) {  // (none may be running when it goes)
+      LBM_HIP(hipStreamSynchronize(b->stream));
+      for (hipStream_t s : b->side)
+        if (s) LBM_HIP(hipStreamSynchronize(s));
+      drop_graphs(b);
+    }
     LBM_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
     int rc = for_launches(m.plan, k, [&](int shape, int32_t q, int32_t tog, int32_t n) {
       const int32_t grid = shape == m.plan.shape ? m.grid : m.rest_grid;

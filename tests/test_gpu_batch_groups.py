@@ -103,3 +103,27 @@ def test_regrouped_jets_keep_their_bits(precision):
             ref = s.moments()
         for key in ref:
             assert np.array_equal(m[key], ref[key]), (p["nx"], n, key)
+
+
+def test_more_group_lengths_than_graphs_are_kept():
+    """Groups of 300 lengths, each captured when it first comes, more than the
+    batch keeps, on two streams: the jets equal themselves run alone."""
+    from paper_1002_3028_amd import lbm
+    lengths = list(range(1, 301)) + [1, 2, 299]
+    jets = [(tiny_params(64, 20, "jet", 1), noisy_inlet(20, 3, 1), 1 << 40),
+            (tiny_params(59, 30, "jet", 0), noisy_inlet(30, 4, 2), 20000)]
+    with lbm.Batch(1 << 26, 2, "fp16") as b:
+        b.set_cohort_bytes(1)  # (a cohort each)
+        slots = [b.admit(*j) for j in jets]
+        for k in lengths:
+            b.run(k)
+        steps = [b.poll(s) for s in slots]
+        assert steps == [sum(lengths), 20000]
+        got = [b.moments(s) for s in slots]
+    for (p, inlet, _), n, m in zip(jets, steps, got):
+        with lbm.Solver(p, "fp16", tile_shape=0, graph_steps=50) as s:
+            s.set_inlet(*inlet)
+            s.step(n)
+            ref = s.moments()
+        for key in ref:
+            assert np.array_equal(m[key], ref[key]), (p["nx"], key)
