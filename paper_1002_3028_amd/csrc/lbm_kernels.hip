@@ -406,6 +406,7 @@ int32_t march_rows(const LaunchJets &jets, int shape, double *us) {
     const int64_t per_cu = (wg + cus - 1) / cus;
     const double t = (double)(k * r + k * (k - 1)) * (0.62 * (per_cu / 2) + 0.41 * (per_cu % 2));
     if (r == 1 || t < best_t) best = r, best_t = t;
+    if (per_cu == 1) break;  // (taller tiles only take longer)
   }
   if (us) *us = best_t;
   return best;
