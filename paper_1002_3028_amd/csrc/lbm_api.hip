@@ -26,13 +26,17 @@ static __device__ __align__(256) RedPartial scratch[kMaxRedBlocks];
 
 namespace {
 // The handle's small results, in pinned host memory that kernels write to
-// directly; the profiles (2 (nx + nr) doubles) follow.
+// directly; the profiles (2 (nx + nr) doubles) of a jet of up to 4096 columns
+// and rows together follow (larger ones get memory when they are asked for:
+// pinning 320 KB took a third of a handle's creation).
 struct HostBlock {
   RedPartial total;   // of the conservation reduction
   int32_t unstable;   // the steps' instability flag
   int32_t bad_input;  // a value handed in was not finite
 };
 constexpr size_t kProfilesAt = 256;
+constexpr size_t kProfilesHeld = size_t(64) << 10;
+size_t profile_bytes(const lbm_config &c) { return 2 * sizeof(double) * ((size_t)c.nx + c.nr); }
 static_assert(sizeof(HostBlock) <= kProfilesAt, "host block");
 }  // namespace
 
@@ -202,7 +206,8 @@ int create_common(const lbm_config *cfg, void *dev_buf, size_t bytes, void *stre
   }
   std::vector<float4> table = make_table(&h->cfg);
   bool ok = hipMalloc(&h->d_desc, sizeof(JetDesc)) == hipSuccess &&
-            hipHostMalloc((void **)&h->host, kProfilesAt + 2 * sizeof(double) * ((size_t)cfg->nx + cfg->nr),
+            hipHostMalloc((void **)&h->host,
+                          kProfilesAt + (profile_bytes(*cfg) <= kProfilesHeld ? profile_bytes(*cfg) : 0),
                           hipHostMallocDefault) == hipSuccess &&
             hipHostGetDevicePointer((void **)&h->d_flag, &h->host->unstable, 0) == hipSuccess &&
             hipMalloc(&h->d_table, table.size() * sizeof(float4)) == hipSuccess;
@@ -529,10 +534,13 @@ int lbm_profiles(lbm_handle *h, double *ux_axis, double *T_axis, double *ux_exit
                  double *T_exit) {
   if (!h) return LBM_EINVAL;
   const size_t nx = h->cfg.nx, nr = h->cfg.nr;
-  const double *p = (const double *)((char *)h->host + kProfilesAt);
-  const int rc = launch_profiles(h->prec, h->stream, h->d_desc, &h->cfg, h->step,
-                                 view_of(h, h->step), (double *)p);
+  void *v = (char *)h->host + kProfilesAt;
+  int rc = profile_bytes(h->cfg) <= kProfilesHeld ? LBM_OK : h->result.get(profile_bytes(h->cfg), &v);
   if (rc) return rc;
+  if ((rc = launch_profiles(h->prec, h->stream, h->d_desc, &h->cfg, h->step, view_of(h, h->step),
+                            (double *)v)))
+    return rc;
+  const double *p = (const double *)v;
   const int st = sync_and_check(h);
   if (st == LBM_EDEVICE) return st;
   if (ux_axis) std::memcpy(ux_axis, p, nx * sizeof(double));

@@ -148,3 +148,22 @@ def test_batch_fields_do_not_wait_for_other_streams():
     assert not waited
     for k in ref:
         assert np.array_equal(m[k], ref[k]), k
+
+
+@pytest.mark.parametrize("nx,nr", [(4000, 96), (4001, 96), (2, 5000), (70000, 3)])
+def test_profiles_of_long_grids(nx, nr):
+    """Profiles of 64 KiB and just more (whose memory comes when they are asked
+    for), and of more than the fields' direct path takes, equal the moments'
+    edges, before and after fields and populations have used the same memory."""
+    from paper_1002_3028_amd import inputs, lbm
+    p = tiny_params(nx, nr, "closed", 1)
+    with lbm.Solver(p, "fp32") as s:
+        s.set_state(*inputs.perturbed_state(nx, nr, seed=nx, noise=0.3))
+        for n in (0, 3, 4):
+            s.step(n)
+            pr, m = s.profiles(), s.moments()
+            again = s.profiles()
+            s.get_populations()
+            for k, ref in (("ux_axis", m["ux"][0]), ("T_axis", m["T"][0]),
+                           ("ux_exit", m["ux"][:, -1]), ("T_exit", m["T"][:, -1])):
+                assert np.array_equal(pr[k], ref) and np.array_equal(again[k], ref), (n, k)
