@@ -241,10 +241,10 @@ int lbm_probe_copy(void *dst, const void *src, size_t bytes, void *hip_stream);
  * active jet by up to k steps: the active jets are grouped into cohorts of
  * at most cohort_bytes of buffers (default 128 MiB, so that the two cohorts
  * in flight at once fill the 256 MiB Infinity Cache; jets that the streams'
- * cohorts hold together are shared out evenly), and each cohort gets k steps
- * of persistent launches, of one to eight steps each, over all its jets (HIP
- * graphs), cohorts alternating between two streams (lbm_batch_set_streams).  A jet
- * stops at its own target step count.  Each jet's result is bitwise the
+ * cohorts hold together are shared out evenly, those that one holds only for
+ * groups long enough), and each cohort gets k steps of persistent launches, of
+ * one to eight steps each, over all its jets (HIP graphs), cohorts alternating
+ * between two streams (lbm_batch_set_streams).  A jet stops at its own target step count.  Each jet's result is bitwise the
  * same as that of the same jet run alone.  `precision` is the batch's
  * storage form; a jet admitted with another (cfg->precision) joins cohorts
  * of its own form, so one batch serves jets of several storage forms. */
@@ -336,7 +336,9 @@ int lbm_tile_shape(int32_t index, int32_t *bx, int32_t *by, int32_t *ny, int32_t
  * (S) run up to S steps per launch with waves that march up strips of
  * 64 - 2 (S - 1) columns (by = 4), or, on small grids, with 16 waves that
  * hold a row each (by = 16), the intermediate states in registers, as
- * bit-identical and on as many edge rules. */
+ * bit-identical and on as many edge rules.  A handle or batch whose shape was
+ * not set chooses by size, storage form and edges, and takes shapes of one or
+ * two steps for what a group of steps leaves after its full launches. */
 int lbm_tile_shape_info(int32_t index, int32_t *info, int32_t n);
 /* Select the launch variant of a handle (synchronises; EINVAL for an unknown
  * index, or any shape but 0 on a single-buffer handle, whose in-place kernel

@@ -1,9 +1,10 @@
 // lbm_api.hip -- single-jet C-ABI (include/lbm.h) on one HIP device.
 //
 // A handle owns (or borrows) two population buffers and a stream, plus a few
-// small device arrays: the descriptor, the property table, the inlet rows and an instability flag.  Steps are enqueued as one
-// launch of the step kernel each, or as HIP graphs of k launches followed
-// by the descriptor advance.
+// small device arrays (the descriptor, the property table, the inlet rows) and
+// pinned memory for small results.  Steps are enqueued as launches of its
+// plan's shapes, or as HIP graphs of the launches of k steps followed by the
+// descriptor advance.
 #include <algorithm>
 #include <mutex>
 
@@ -18,10 +19,10 @@ constexpr int kMaxRedBlocks = 1024;
 }  // namespace
 
 // Partial sums of the no-allocation FP64 conservation reduction
-// (lbm_conservation_noalloc): one per reduction workgroup.  32 KB.  Each device holds its own copy until the process ends.  In host
-// code the name stands for no device address: host code reaches the array
-// only through the pointer that hipGetSymbolAddress returns for the current
-// device (scratch_on).
+// (lbm_conservation_noalloc): one per reduction workgroup, 32 KB.  Each device
+// holds its own copy until the process ends.  In host code the name stands for
+// no device address: host code reaches the array only through the pointer that
+// hipGetSymbolAddress returns for the current device (scratch_on).
 static __device__ __align__(256) RedPartial scratch[kMaxRedBlocks];
 
 namespace {

@@ -2,12 +2,13 @@
 // Population buffers are carved out of one device arena (the HBM budget) by
 // a first-fit allocator.  Active jets are grouped into cohorts whose buffers
 // together fit the Infinity Cache; a run of k steps advances cohort after
-// cohort, each with one launch per step over a flat tile list covering the
-// cohort's jets, so every cohort's working set stays cache-resident for its
-// k steps.  Each cohort has fixed device arrays (descriptors, tile prefix
-// sums, header) and the launch configuration never changes with the set of
-// jets, so the captured graph of k steps of a cohort is replayed as jets come
-// and go.
+// cohort, each with launches of one to eight steps over a flat tile list
+// covering the cohort's jets, so every cohort's working set stays
+// cache-resident for its k steps.  Each cohort has fixed device arrays
+// (descriptors, tile prefix sums, header) and a launch takes the workgroups
+// that the device holds at once, so the captured graph of k steps of a cohort
+// is replayed as jets come and go, as long as they leave the cohort's plan
+// (default_plan) the same.
 //
 // A batch holds jets of several storage forms (the batch's own unless a
 // jet's configuration names another); each cohort holds one form, so that

@@ -287,6 +287,16 @@ const TileShape *tile_shapes(int *count) {
 // against 17.0 us per step, 1024 x 512 between two walls: 8.6 against 8.8)
 // and one step in 16 bits (12.4 / 17.6, 7.7 / 10.1).
 //
+// Property tables that LDS does not hold (more than 256 entries) make a march
+// wait for its gathers: 9.6 us per step against 8.8 on 2048 x 512, 15.5
+// against 14.1 on 3000 x 700, 37.9 against 28.7 on 4096 x 1024 (FP16 11.0
+// against 10.5, 18.3 against 17.2, 30.2 against 28.5).  That is still less
+// than any other shape takes on such a jet (the two-step kernel 12.7, 20.6 and
+// 56.2, FP16 one step 12.0, 18.7 and 32.1; small grids take the same time with
+// either), so the table's size does not enter the rule.  One such jet among 16
+// of 512 x 128 takes its cohort from 11.6 to 12.9 us per step (two steps per
+// launch 14.8).
+//
 // A launch of fewer steps than its shape holds costs more than its share (a
 // march of one step on 2048 x 512 takes 23.4 us, of two 30.3), so that a
 // group's last steps, or a caller's single ones, take another shape where that

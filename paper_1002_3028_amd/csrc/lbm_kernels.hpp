@@ -79,8 +79,9 @@ __device__ __forceinline__ TileWalk tile_walk(int32_t ntiles) {
 // Workgroups walk the tile list as tile_walk() assigns it.  W is the
 // occupancy target (waves per SIMD) for register allocation; CP selects non-temporal stores (bit 0) and loads (bit 1).
 // The jet's state after s steps lives in buf[(s + flip) & 1], where flip is
-// the descriptor's value toggled by `tog` (the parity of the two-step
-// launches issued since the descriptor was last advanced); the step taken
+// the descriptor's value toggled by `tog` (the parity of the launches of an
+// even number of steps issued since the descriptor was last advanced, each of
+// which swaps the buffers' roles); the step taken
 // here is step0 + koff, skipped once the jet reaches its target.  `nsteps`
 // is unused (the two-step kernel below shares this signature).
 // ---------------------------------------------------------------------------

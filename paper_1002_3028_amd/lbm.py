@@ -358,7 +358,7 @@ class Solver:
 
 
 class Batch:
-    """Many resident jets advanced by one persistent launch per step."""
+    """Many resident jets advanced by persistent launches of one to eight steps."""
 
     def __init__(self, budget_bytes: int, max_slots: int, precision: str = "fp32", stream=None,
                  layout: str = "two"):

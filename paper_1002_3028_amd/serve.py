@@ -4,8 +4,8 @@ Requests (a jet configuration, its inlet rows and a step count) arrive over
 time.  A request is admitted as soon as it has arrived, a slot is free and
 its two population buffers fit the HBM budget; its populations stay resident
 on the device until it finishes.  All resident jets advance together, k
-steps per group, in one persistent launch per step for each cohort of
-jets (one storage form per cohort).  The loop queues each
+steps per group, in persistent launches of one to eight steps for each cohort
+of jets (one storage form per cohort).  The loop queues each
 group before it handles the previous one, so the device is not left idle
 while the host works: the jets that reached their step count in the previous
 group return their centreline and exit-column profiles of u_x and T and free
