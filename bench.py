@@ -234,10 +234,11 @@ def roofline_block(prec, info, nodes, ms_step, traffic_name, trace_name=None, ta
 
 def bench_batch(n_jets=64, steps=5000, precision="fp32", looped=True):
     """64 jets of uneven sizes (seed 2) advanced together, in persistent
-    launches of one to eight steps per cohort, with the launch configuration the batch tuner picks for this set (tile shape, grid,
-    cohort size, streams; tuned once and cached) and, for comparison, with
-    the batch's defaults; with `looped`, against the same jets run one after
-    another through the single-jet path.  Aggregate GLUPS of each."""
+    launches of one to eight steps per cohort, with the launch configuration
+    the batch tuner picks for this set (tile shape, grid, cohort size, streams;
+    tuned once and cached) and, for comparison, with the batch's defaults; with
+    `looped`, against the same jets run one after another through the
+    single-jet path.  Aggregate GLUPS of each."""
     import torch
     from paper_1002_3028_amd import autotune, inputs, lbm
 
