@@ -88,8 +88,7 @@ struct alignas(16) JetDesc {
   int64_t step0;           // step count of the launch with koff = 0
   int64_t target;          // the jet stops at this step count
   int32_t nx, nr, pitch;
-  int32_t tiles_x, ntiles;         // tiles per row and of the jet in launches of one or two steps
-  int32_t mtiles_x, mtiles;        // and in launches of more
+  int32_t tiles_x;                 // tiles per row in launches of one or two steps
   int32_t n_t, table_n, hoop, slot;
   int32_t bc[4];
   float r0, nu0, alpha0, c18;      // c18 = 18 (C_s Delta)^2
@@ -97,8 +96,11 @@ struct alignas(16) JetDesc {
   float rho_ref, g4_ref;
   int32_t flip;                    // toggled by every launch that advances an even number of steps
   int32_t tile_rows;               // rows of one wave's tile (march_kernel)
+  int32_t ntiles;                  // tiles of the jet in launches of one or two steps
   int32_t tile_steps;              // steps a launch of more than two advances
+  int32_t mtiles_x, mtiles;        // tiles per row and of the jet in such launches
   int32_t cus;                     // of the device: workgroups of one filling (march_kernel)
+  int32_t pad;
   float wallT[4];                  // NaN: adiabatic
   float eq[4][4];                  // EQ side: rho, ux, ur, T
 };
